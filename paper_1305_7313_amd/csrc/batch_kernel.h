@@ -146,9 +146,9 @@ __device__ __noinline__ void batch_plane_unit(void* slot, const BatchSys* Sp, co
   A.n1 = NN;
   A.nb = g.ti * g.tj;
   if (g.stage == BS_P1)
-    plane_body<T, NN, NN, kBatchW, Sh::PSPLIT, PLANE_PAIR_FWD>(A, u, smem, tw, tw);
+    plane_body<T, NN, NN, kBatchW, Sh::PSPLIT, PLANE_PAIR_FWD>(A, u, smem, tw, tw, [] {});
   else
-    plane_body<T, NN, NN, kBatchW, Sh::PSPLIT, PLANE_INV>(A, u, smem, tw, tw);
+    plane_body<T, NN, NN, kBatchW, Sh::PSPLIT, PLANE_INV>(A, u, smem, tw, tw, [] {});
 }
 
 template <typename T, int NN, int OCC>
@@ -163,7 +163,7 @@ __device__ __noinline__ void batch_pencil_unit(void* slot, const BatchSys* Sp, c
   A.n2 = NN;
   A.n3 = NN;
   A.count = gp->ti * gp->tj;
-  pencil_body<T, NN, Sh::CB, kBatchW, Sh::CSPLIT, PENCIL_FKI>(A, u, smem, tw, red);
+  pencil_body<T, NN, Sh::CB, kBatchW, Sh::CSPLIT, PENCIL_FKI>(A, u, smem, tw, red, [] {});
 }
 
 template <typename T, int OCC>

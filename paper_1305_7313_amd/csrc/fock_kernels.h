@@ -85,6 +85,31 @@ struct PlaneArgs {
 // pair-density data; entries outside are zero and are neither stored nor read.
 template <int N2> __device__ __forceinline__ bool live_row(int i2, int h) { return i2 <= h || i2 >= N2 - h; }
 
+// How P1 walks a tile and stores its partly live lines.
+// strip: the workgroups of one plane take `strip` occupied orbitals at a time
+//   against every target.  The operand planes in flight on one XCD are then
+//   about strip plus a few, and they and the stores passing through its 4 MB L2
+//   do not push each other out: a 32 x 32 FP32 tile holds 64 planes of 74-98 KB
+//   per i1.  1: one occupied orbital after the other, where the tile's planes
+//   fit in L2 anyway.
+// lines: store a 128-byte line with a live entry whole.  A partly written line
+//   costs the memory a read-modify-write, a whole one 12-15% more bytes.
+// Both measured in whole applies (P1 us, per-entry against whole lines; strip 1
+// against the value taken): FP32 48 1195 / 1107, 64 2837 / 2550, 72 4779 / 5151,
+// 96 4552 / 4884 (strip 8: 4458), 96 x 128 13723 / 14864 (strip 8: 13330);
+// FP64 48 931 / 793, 64 8538 / 8913, 72 3688 / 4070, 96 4429 / 4236 (strip 4:
+// 4165), 96 x 128 9036 / 8723 (strip 4: 8618).
+struct P1Tune {
+  int strip;
+  bool lines;
+};
+constexpr P1Tune p1_tune(int tbytes, int n2, int n3, bool gamma) {
+  // Gamma tiles (128 pairs, half the orbitals) have the bandwidth for the extra
+  // bytes also at FP64 64: 1038 / 861
+  if (tbytes == 8) return P1Tune{n3 >= 96 ? 4 : 1, n2 <= 48 || n3 >= 96 || (gamma && n3 == 64)};
+  return P1Tune{n3 >= 96 ? 8 : n3 <= 48 ? 4 : 1, n3 <= 64};
+}
+
 // Slot of pair (ii, jj), ii <= jj, in the pair buffer of a diagonal tile.
 __host__ __device__ constexpr int tri_slot(int ii, int jj) { return jj * (jj + 1) / 2 + ii; }
 
@@ -192,9 +217,9 @@ template <typename T, int N2, int N3, int W, bool SPLIT> struct PlaneGeom {
   static constexpr int NV = Rw::NV > Cl::NV ? Rw::NV : Cl::NV;
 };
 
-template <typename T, int N2, int N3, int W, bool SPLIT, int MODE>
+template <typename T, int N2, int N3, int W, bool SPLIT, int MODE, class Stage>
 __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned char* smem, const cx<T>* tw2,
-                                           const cx<T>* tw3) {
+                                           const cx<T>* tw3, Stage&& stage) {
   using Cfg = PlaneGeom<T, N2, N3, W, SPLIT>;
   constexpr bool PAD = plane_tile_pad<T, N3>();
   // On the compact (unpadded) tile, the row pass that touches only LDS walks
@@ -231,16 +256,25 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       while (tri_slot(0, jj + 1) <= rem) ++jj;
       ii = rem - tri_slot(0, jj);
     } else {
-      ii = rem / A.tj;
-      jj = rem - ii * A.tj;
+      // strips of occupied orbitals, the targets walked inside a strip (P1Tune)
+      constexpr int S = p1_tune(sizeof(T), N2, N3, gam).strip;
+      const int strip = rem / (S * A.tj), r = rem - strip * (S * A.tj);
+      const int h = A.ti - strip * S < S ? A.ti - strip * S : S;
+      jj = r / h;
+      ii = strip * S + r - jj * h;
     }
     const cx<T>* pb = reinterpret_cast<const cx<T>*>(A.bsrc) + (long long)(A.j0 + jj) * N + (long long)i1 * PLANE;
+    const int hc = A.live ? A.live[t % N3] : N2;  // a column pass: column t % N3 for every stored value
+    cx<T> b[Cfg::NV];
     if constexpr (MODE == PLANE_PAIR_FWD) {
       const cx<T>* pa = reinterpret_cast<const cx<T>*>(A.a) + (long long)(A.i0 + ii) * N + (long long)i1 * PLANE;
       for_inputs<R0>(t, [&](int e, int row, int col) {
         const int p = row * N3 + col;
-        v[e] = cmulc<T>(pa[p], pb[p]);
+        v[e] = pa[p];
+        b[e] = pb[p];
       });
+      stage();
+      for_inputs<R0>(t, [&](int e, int row, int col) { v[e] = cmulc<T>(v[e], b[e]); });
     } else {
       // real phi_i is one component of the packed occupied array
       const int i = A.i0 + ii;
@@ -248,9 +282,11 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       const bool hi = i & 1;
       for_inputs<R0>(t, [&](int e, int row, int col) {
         const int p = row * N3 + col;
-        const cx<T> a = pa[p];
-        v[e] = cscale<T>(pb[p], hi ? a.y : a.x);
+        v[e] = pa[p];
+        b[e] = pb[p];
       });
+      stage();
+      for_inputs<R0>(t, [&](int e, int row, int col) { v[e] = cscale<T>(b[e], hi ? v[e].y : v[e].x); });
     }
     pass_compute<R0, -1, T>(v, tw3, t);
     exchange<R0, R1, N3, SPLIT, T, PAD>(v, smem, t);
@@ -259,19 +295,15 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     pass_compute<C0, -1, T>(v, tw2, t);
     exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
     pass_compute<C1, -1, T>(v, tw2, t);
-    cx<T>* pw = reinterpret_cast<cx<T>*>(A.w) + (long long)rem * N + (long long)i1 * PLANE;
-    const int hc = A.live ? A.live[t % N3] : N2;  // a column pass: column t % N3 for every value
-    // Dead entries are not stored.  On the 128-wide rows a 128-byte line
-    // with a live entry is written whole (the dead entries' values are never
-    // read), since a partly written line costs the memory a read-modify-write;
-    // measured there: P1 -7% (FP64) and -1.4% (FP32), where the 96-wide FP32
-    // and 64-wide FP64 rows lose 3% and 9% to the extra bytes and keep their
-    // per-entry stores.  The LINE lanes of an aligned lane group hold one
-    // line of one row (consecutive columns from a multiple of N3).
+    const int slot = A.tri ? rem : ii * A.tj + jj;
+    cx<T>* pw = reinterpret_cast<cx<T>*>(A.w) + (long long)slot * N + (long long)i1 * PLANE;
+    // Dead entries are not stored, or (P1Tune::lines) a 128-byte line with a
+    // live entry is written whole: the dead entries' values are never read.
+    // The LINE lanes of an aligned lane group hold consecutive columns.
     constexpr int LINE = 128 / (int)sizeof(cx<T>);
     for_outputs<C1>(t, [&](int e, int row, int col) {
       bool st = live_row<N2>(row, hc);
-      if constexpr (N3 == 128) {
+      if constexpr (p1_tune(sizeof(T), N2, N3, gam).lines) {
         if (A.live) {
           const unsigned long long m = __ballot(st);
           st = ((m >> ((t & 63) & ~(LINE - 1))) & ((1ull << LINE) - 1)) != 0;
@@ -291,6 +323,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     const int o0 = mir ? A.j0 : A.i0;
     const cx<T>* src = reinterpret_cast<const cx<T>*>(mir ? A.bsrc : A.a);
     const int k0 = A.tri && mir ? bi + 1 : 0, k1 = A.tri && !mir ? bi + 1 : nloop;
+    stage();
     // every entry is read here: skipping the dead columns (zeros) measured
     // slower in these register-heavy passes than reading them
     cx<T> s[R1::NV];
@@ -349,6 +382,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       else k1 = gtri_count(A.ti, bi);
     }
     const int hc = A.live ? A.live[t % N3] : N2;  // entries outside are zero: not read
+    stage();
     cx<T> s[R1::NV];
 #pragma unroll
     for (int e = 0; e < R1::NV; ++e) s[e] = mk<T>(T(0), T(0));
@@ -406,6 +440,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     const int ob = lid / A.n1, i1 = lid - (lid / A.n1) * A.n1;
     cx<T>* px = reinterpret_cast<cx<T>*>(A.x) + (long long)ob * N + (long long)i1 * PLANE;
     for_inputs<R0>(t, [&](int e, int row, int col) { v[e] = px[row * N3 + col]; });
+    stage();
     pass_compute<R0, -1, T>(v, tw3, t);
     exchange<R0, R1, N3, SPLIT, T, PAD>(v, smem, t);
     pass_compute<R1, -1, T>(v, tw3, t);
@@ -415,6 +450,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     pass_compute<C1, -1, T>(v, tw2, t);
     for_outputs<C1>(t, [&](int e, int row, int col) { px[row * N3 + col] = v[e]; });
   } else if constexpr (MODE == PLANE_DENS) {
+    stage();
     // sum over this group's bands of f_b * fscale * |psi_b(r)|^2 on plane i1
     const int G = A.ngrp;
     const int i1 = lid / G, g = lid - (lid / G) * G;
@@ -444,6 +480,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     // back into place.  V's plane stays in registers for the group's bands.
     const int G = A.ngrp;
     const int i1 = lid / G, g = lid - (lid / G) * G;
+    stage();
     const T* pv = reinterpret_cast<const T*>(A.vloc) + (long long)i1 * PLANE;
     T vr[R1::NV];
     for_outputs<R1>(t, [&](int e, int row, int col) { vr[e] = pv[row * N3 + col]; });
@@ -475,6 +512,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     for_inputs<C0>(t, [&](int e, int row, int col) {
       v[e] = live_row<N2>(row, hc) ? px[row * N3 + col] : mk<T>(T(0), T(0));
     });
+    stage();
     pass_compute<C0, +1, T>(v, tw2, t);
     exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
     pass_compute<C1, +1, T>(v, tw2, t);
@@ -531,7 +569,7 @@ constexpr PlaneTune plane_tune(int tbytes, int n2, int n3, int mode) {
     // padded exchange layouts: three planes per CU in flight where two
     // workgroups of 720 threads (12 waves) fit (16-system batch 1086 -> 1071
     // ms, 72^3 k-mesh 8723 -> 8246 ms)
-    if (p1) return PlaneTune{504, false, 1};
+    if (p1) return PlaneTune{504, false, 6};  // at most 80 registers, else two planes per CU
     if (fwdmac || mirror) return PlaneTune{720, false, 1};
     return inv ? PlaneTune{504, true, 1} : PlaneTune{576, false, 1};
   }
@@ -554,10 +592,18 @@ __global__ __launch_bounds__(W, MINB) void plane_kernel(PlaneArgs A) {
   __shared__ __align__(16) unsigned char smem[G::XBYTES];
   __shared__ cx<T> tw2[N2];
   __shared__ cx<T> tw3[N3];
-  load_table<T>(tw2, A.tw2, N2);
-  load_table<T>(tw3, A.tw3, N3);
-  __syncthreads();
-  plane_body<T, N2, N3, W, SPLIT, MODE>(A, xcd_logical(blockIdx.x, gridDim.x), smem, tw2, tw3);
+  // The twiddles are loaded first and stored to LDS once the body has issued
+  // its first operand loads: one exposed memory latency per workgroup, not two.
+  static_assert(W >= N2 && W >= N3, "one table entry per thread");
+  const int t = threadIdx.x;
+  cx<T> w2 = mk<T>(T(0), T(0)), w3 = w2;
+  if (t < N2) w2 = reinterpret_cast<const cx<T>*>(A.tw2)[t];
+  if (t < N3) w3 = reinterpret_cast<const cx<T>*>(A.tw3)[t];
+  plane_body<T, N2, N3, W, SPLIT, MODE>(A, xcd_logical(blockIdx.x, gridDim.x), smem, tw2, tw3, [&] {
+    if (t < N2) tw2[t] = w2;
+    if (t < N3) tw3[t] = w3;
+    __syncthreads();
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -593,9 +639,9 @@ template <typename T, int N1, int CB, int W, bool SPLIT> struct PencilGeom {
   static constexpr int NV = Ax::NV;
 };
 
-template <typename T, int N1, int CB, int W, bool SPLIT, int MODE>
+template <typename T, int N1, int CB, int W, bool SPLIT, int MODE, class Stage>
 __device__ __forceinline__ void pencil_body(const PencilArgs& A, int lid, unsigned char* smem, const cx<T>* tw1,
-                                            double* red) {
+                                            double* red, Stage&& stage) {
   using Cfg = PencilGeom<T, N1, CB, W, SPLIT>;
   using P0 = typename Cfg::Ax::P0;
   using P1 = typename Cfg::Ax::P1;
@@ -625,6 +671,7 @@ __device__ __forceinline__ void pencil_body(const PencilArgs& A, int lid, unsign
     });
   else
     for_inputs<P0>(t, [&](int e, int row, int col) { v[e] = base[(long long)row * plane + col]; });
+  stage();
   pass_compute<P0, DIR0, T>(v, tw1, t);
   exchange<P0, P1, CB, SPLIT, T>(v, smem, t);
   pass_compute<P1, DIR0, T>(v, tw1, t);
@@ -725,9 +772,15 @@ __global__ __launch_bounds__(W, MINB) void pencil_kernel(PencilArgs A) {
   __shared__ __align__(16) unsigned char smem[G::XBYTES];
   __shared__ cx<T> tw1[N1];
   __shared__ double red[(W + 63) / 64];
-  load_table<T>(tw1, A.tw1, N1);
-  __syncthreads();
-  pencil_body<T, N1, CB, W, SPLIT, MODE>(A, xcd_logical(blockIdx.x, gridDim.x), smem, tw1, red);
+  // table first, operand loads next, then the table's LDS copy (see plane_kernel)
+  static_assert(W >= N1, "one table entry per thread");
+  const int t = threadIdx.x;
+  cx<T> w1 = mk<T>(T(0), T(0));
+  if (t < N1) w1 = reinterpret_cast<const cx<T>*>(A.tw1)[t];
+  pencil_body<T, N1, CB, W, SPLIT, MODE>(A, xcd_logical(blockIdx.x, gridDim.x), smem, tw1, red, [&] {
+    if (t < N1) tw1[t] = w1;
+    __syncthreads();
+  });
 }
 
 // ---------------------------------------------------------------------------
