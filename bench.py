@@ -300,28 +300,37 @@ def gamma_step_bytes(n, N, bpc, ti_max=16, tj_max=8, lf=1.0):
     return acc
 
 
-def band_step_bytes(nb, N, npw, bpc, force, chunk=64, groups=8):
-    """Algorithmic bytes per step of the band loops (chunks of 64 bands, 8 band
-    groups per plane), per kernel class."""
-    acc = {}
+def sphere_plane(miller, n, bpc):
+    """(lines, blocks) of the sphere's plane columns: the 128-byte lines of a
+    plane that hold one and the blocks of 8 columns along axis 3."""
+    n2, n3 = n[1], n[2]
+    live = np.full(n3, -1)
+    np.maximum.at(live, miller[:, 2] % n3, np.abs(miller[:, 1]))
+    i2 = np.arange(n2)[:, None]
+    mask = (live >= 0) & ((i2 <= live) | (i2 >= n2 - live))
+    return (int(mask.reshape(-1, 128 // bpc).any(axis=1).sum()), int((live >= 0).reshape(-1, 8).any(axis=1).sum()))
 
-    def add(k, nbytes):
-        a = acc.setdefault(k, [0.0, 0])
-        a[0] += nbytes
-        a[1] += 1
 
-    for b0 in range(0, nb, chunk):
-        n = min(chunk, nb - b0)
-        add("a1_scatter", n * N * bpc + 2 * n * npw * bpc + npw * 4)  # clear, coefficients in and out, slots
-        add("a1_pencil_inv", 2 * n * N * bpc)
-        if force:
-            add("band_plane_vmul", 2 * n * N * bpc + groups * N * bpc // 2)  # V once per band group
-            add("a7_pencil_fwd", 2 * n * N * bpc)
-            add("band_force_gather", 3 * n * npw * bpc + npw * 4)
-        else:
-            add("band_plane_density", n * N * bpc + groups * N * 8 * (2 if b0 else 1))
-    if not force:
-        add("reduce", (groups + 1) * N * 8)
+def band_step_bytes(nb, n, miller, bpc, force):
+    """Algorithmic bytes per step of the band loops, per kernel class: sphere
+    pass (coefficients to live lines), axis-2 pass (live rows to every row of
+    the live column blocks), rows along axis 3, and for the force the way back."""
+    N, npw = n[0] * n[1] * n[2], len(miller)
+    nl, nc = sphere_plane(miller, n, bpc)
+    lines, cols = 128.0 * nl * n[0], 8.0 * nc * n[0] * n[1] * bpc  # bytes per band
+    chunk = max(1, min(64, (256 << 20) // int(cols)))
+    parts = -(-nb // chunk)
+    rb = {24: 64, 48: 32, 64: 32, 72: 32, 96: 16, 128: 8}[n[2]]
+    nrb = n[0] * n[1] // rb
+    acc = {"a1_pencil_inv": [nb * (lines + npw * bpc), parts], "a1_plane_inv": [nb * (lines + cols), parts]}
+    if force:
+        acc["band_plane_vmul"] = [nb * 2 * cols + parts * N * bpc / 2, parts]
+        acc["a7_plane_fwd"] = [nb * (cols + lines), parts]
+        acc["a7_pencil_fwd"] = [nb * (lines + 2 * npw * bpc), parts]
+    else:
+        groups = min(8, -(-nb // parts), -(-2048 // nrb))
+        acc["band_plane_density"] = [nb * cols + groups * N * 8.0 * (2 * parts - 1), parts]
+        acc["reduce"] = [(groups + 1) * N * 8.0, 1]
     return acc
 
 
@@ -647,7 +656,7 @@ def band_loops(name, args, cpu):
                       "bands": nb}, "cpu_baseline": cpu or None}
     if not args.no_trace:
         tr = traced(fock, step, args.steps)
-        acc = band_step_bytes(nb, N, s.npw, 16, force)
+        acc = band_step_bytes(nb, s.n, s.miller, 16, force)
         rec["roofline"] = roofline(tr, acc, args.steps, name)
         rec["kernels"] = {k: {"ms_per_step": round(v[0] / args.steps, 4), "launches_per_step": v[1] / args.steps}
                           for k, v in tr.items() if v[1]}

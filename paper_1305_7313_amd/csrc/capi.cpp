@@ -34,12 +34,12 @@ fock_status fail(fock_status s, const std::string& msg) {
 // ---------------------------------------------------------------------------
 enum KClass : int {
   KC_A1_SCATTER = 0, KC_A1_PENCIL, KC_A1_PLANE, KC_P1, KC_P2, KC_P2E, KC_P3, KC_P3B,
-  KC_A7_PLANE, KC_A7_PENCIL, KC_A7_GATHER, KC_REDUCE, KC_ZERO, KC_BAND_DENS, KC_BAND_VMUL, KC_BAND_GATHER, KC_COUNT
+  KC_A7_PLANE, KC_A7_PENCIL, KC_A7_GATHER, KC_REDUCE, KC_ZERO, KC_BAND_DENS, KC_BAND_VMUL, KC_COUNT
 };
 const char* const kClassNames[KC_COUNT] = {
     "a1_scatter", "a1_pencil_inv", "a1_plane_inv", "p1_pair_plane_fwd", "p2_pencil_kernel",
     "p2_pencil_energy", "p3_plane_inv_mac", "p3_second", "a7_plane_fwd", "a7_pencil_fwd", "a7_gather",
-    "reduce", "zero_fill", "band_plane_density", "band_plane_vmul", "band_force_gather"};
+    "reduce", "zero_fill", "band_plane_density", "band_plane_vmul"};
 
 struct Tracer {
   std::mutex m;
@@ -98,12 +98,17 @@ struct Plan {
   // (after the transform over the plane axes) at rows |m2| > d_live[i3]; -1:
   // none in that column.  Null when S - S wraps on this grid.
   signed char* d_live = nullptr;
+  // Sphere columns of the one-dimensional passes (SphereTables); null in a plan
+  // of the allocation-free call, whose transforms clear, scatter and gather.
+  SphereTables sph{nullptr, nullptr, nullptr, nullptr, 0, 0};
+  void* d_sph = nullptr;  // one allocation behind the four tables
   bool owns = true;  // false: the device tables live in memory the plan does not own
   ~Plan() {
     if (!owns) return;
     (void)hipSetDevice(device);
     if (d_slot) (void)hipFree(d_slot);
     if (d_live) (void)hipFree(d_live);
+    if (d_sph) (void)hipFree(d_sph);
     for (auto p : d_tw)
       if (p) (void)hipFree(p);
   }
@@ -292,6 +297,61 @@ fock_status sphere_tables(const fock_cell* cell, std::vector<int>* slot, std::ve
   return FOCK_OK;
 }
 
+// Host image of the SphereTables of a cell: the four tables one behind the
+// other, each at a multiple of 16 bytes.
+struct SphereHost {
+  std::vector<unsigned char> bytes;
+  size_t lines, coef, live, cols;
+  int nl, nc;
+};
+SphereHost sphere_columns(const fock_cell* cell, const std::vector<int>& slot, int cplx_bytes) {
+  const int n1 = cell->n[0], n2 = cell->n[1], n3 = cell->n[2], plane = n2 * n3;
+  const int line = 128 / cplx_bytes;
+  // per column i3 the largest |m2| of the sphere's projection
+  std::vector<signed char> live((size_t)n3, (signed char)-1);
+  for (int p = 0; p < cell->npw; ++p) {
+    const int m2 = std::abs(cell->miller[3 * p + 1]);
+    const int i3 = (cell->miller[3 * p + 2] % n3 + n3) % n3;
+    if (m2 > live[i3]) live[i3] = (signed char)m2;
+  }
+  std::vector<int> index((size_t)(plane / line), -1), lines, cols;
+  for (int l = 0; l < plane / line; ++l)
+    for (int c = 0; c < line; ++c) {
+      const int i2 = (l * line + c) / n3, h = live[(l * line + c) % n3];
+      if (h >= 0 && (i2 <= h || i2 >= n2 - h)) {
+        index[l] = (int)lines.size();
+        lines.push_back(l);
+        break;
+      }
+    }
+  for (int k = 0; k < n3 / 8; ++k)
+    for (int c = 0; c < 8; ++c)
+      if (live[8 * k + c] >= 0) {
+        cols.push_back(k);
+        break;
+      }
+  SphereHost H;
+  H.nl = (int)lines.size();
+  H.nc = (int)cols.size();
+  const int ncol = H.nl * line;
+  std::vector<int> coef((size_t)n1 * ncol, -1);
+  for (int p = 0; p < cell->npw; ++p) {
+    const int i1 = slot[p] / plane, q = slot[p] - i1 * plane;
+    coef[(size_t)i1 * ncol + index[q / line] * line + q % line] = p;
+  }
+  auto put = [&](const void* src, size_t n) {
+    const size_t at = H.bytes.size();
+    H.bytes.resize(at + (n + 15) / 16 * 16);
+    std::memcpy(H.bytes.data() + at, src, n);
+    return at;
+  };
+  H.lines = put(lines.data(), sizeof(int) * lines.size());
+  H.coef = put(coef.data(), sizeof(int) * coef.size());
+  H.live = put(live.data(), live.size());
+  H.cols = put(cols.data(), sizeof(int) * cols.size());
+  return H;
+}
+
 fock_status get_plan(const fock_cell* cell, int dtype, std::shared_ptr<Plan>* out) {
   double b[3][3], omega = 0.0;
   fock_status st0 = check_plan_cell(cell, dtype, b, &omega);
@@ -332,6 +392,15 @@ fock_status get_plan(const fock_cell* cell, int dtype, std::shared_ptr<Plan>* ou
   if (e == hipSuccess && has_live) {
     e = hipMalloc(&p->d_live, live.size());
     if (e == hipSuccess) e = hipMemcpy(p->d_live, live.data(), live.size(), hipMemcpyHostToDevice);
+  }
+  if (e == hipSuccess) {
+    const SphereHost H = sphere_columns(cell, slot, dtype == FOCK_C128 ? 16 : 8);
+    e = hipMalloc(&p->d_sph, H.bytes.size());
+    if (e == hipSuccess) e = hipMemcpy(p->d_sph, H.bytes.data(), H.bytes.size(), hipMemcpyHostToDevice);
+    const char* d = static_cast<const char*>(p->d_sph);
+    p->sph = SphereTables{reinterpret_cast<const int*>(d + H.lines), reinterpret_cast<const int*>(d + H.coef),
+                          reinterpret_cast<const signed char*>(d + H.live), reinterpret_cast<const int*>(d + H.cols),
+                          H.nl, H.nc};
   }
   for (int k = 0; k < 3 && e == hipSuccess; ++k) e = upload_twiddles(cell->n[k], dtype, &p->d_tw[k]);
   if (e != hipSuccess) return fail(FOCK_E_HIP, std::string("plan upload: ") + hipGetErrorString(e));
@@ -468,8 +537,51 @@ struct Engine {
     ngroups = P.n[1] * P.n[2] / pencil_columns(P.n[0], (int)sizeof(T));
   }
 
+  // Arguments of the sphere pass over a block of boxes; *nblocks: its grid.
+  SphereArgs sphere_args(void* box, int nb, int* nblocks) const {
+    constexpr int line = 128 / (int)sizeof(cx<T>);
+    SphereArgs a{};
+    a.tab = P.sph;
+    a.box = box;
+    a.tw1 = P.d_tw[0];
+    a.N = P.N;
+    a.n2 = P.n[1];
+    a.n3 = P.n[2];
+    const int per = pencil_columns(P.n[0], (int)sizeof(T)) / line;
+    a.ngrp = (P.sph.nl + per - 1) / per;
+    *nblocks = nb * a.ngrp;
+    return a;
+  }
+
+  // Plane pass of orbitals, in place (PLANE_INV, PLANE_FWD): only the sphere's
+  // columns are read or written on the reciprocal side.
+  fock_status plane_sphere(int mode, void* box, int nb) {
+    PlaneArgs la{};
+    la.x = box;
+    la.tw2 = P.d_tw[1];
+    la.tw3 = P.d_tw[2];
+    la.N = P.N;
+    la.n1 = P.n[0];
+    la.nb = nb;
+    la.live = P.sph.live;
+    FX_TRACE(mode == PLANE_INV ? KC_A1_PLANE : KC_A7_PLANE);
+    FX_HIP(launch_plane<T>(mode, P.n[1], P.n[2], la, nb * P.n[0], s));
+    return FOCK_OK;
+  }
+
   fock_status to_real_space(const void* c, int ld, int nb, void* box) {
     if (nb <= 0) return FOCK_OK;
+    if (P.d_sph) {
+      {
+        FX_TRACE(KC_A1_PENCIL);
+        int g = 0;
+        SphereArgs sa = sphere_args(box, nb, &g);
+        sa.c = c;
+        sa.ldc = ld;
+        FX_HIP(launch_sphere<T>(SPHERE_INV, P.n[0], sa, g, s));
+      }
+      return plane_sphere(PLANE_INV, box, nb);
+    }
     {
       FX_TRACE(KC_A1_SCATTER);
       FX_HIP(launch_zero<T>(box, P.N * nb, s));
@@ -581,8 +693,23 @@ struct Engine {
   // acc[0..nj) (real space) -> forward FFT -> sphere rows j0.. of out, scaled.
   fock_status finish(void* acc, int nj, int j0, void* out, int ldo, double s0, const double* wout,
                      const double* gscale) {
-    fock_status st = transform(acc, nj, -1);
-    if (st != FOCK_OK) return st;
+    fock_status st;
+    if (P.d_sph) {
+      if (nj <= 0) return FOCK_OK;
+      if ((st = plane_sphere(PLANE_FWD, acc, nj)) != FOCK_OK) return st;
+      FX_TRACE(KC_A7_PENCIL);
+      int g = 0;
+      SphereArgs sa = sphere_args(acc, nj, &g);
+      sa.out = out;
+      sa.ldo = ldo;
+      sa.s0 = s0;
+      sa.w = wout;
+      sa.g = gscale;
+      sa.j0 = j0;
+      FX_HIP(launch_sphere<T>(SPHERE_FWD, P.n[0], sa, g, s));
+      return FOCK_OK;
+    }
+    if ((st = transform(acc, nj, -1)) != FOCK_OK) return st;
     char* o = static_cast<char*>(out) + (size_t)j0 * ldo * sizeof(cx<T>);
     FX_TRACE(KC_A7_GATHER);
     FX_HIP(launch_gather<T>(acc, P.N, P.d_slot, P.npw, nj, o, ldo, s0, wout, j0, gscale, s));
@@ -948,11 +1075,15 @@ fock_status apply_gamma_impl(const fock_cell* cell, const Plan& P, const fock_or
   void* acc = ws + L.phiB;  // packed accumulators [m][N]
   const size_t box = (size_t)P.N * sizeof(cx<T>);
   {
-    FX_TRACE(KC_A1_SCATTER);
-    FX_HIP(launch_zero<T>(pk, P.N * m, s));
-    FX_HIP(launch_scatter_pack<T>(o->c, o->ld, P.d_slot, P.npw, n, pk, P.N, s));
+    FX_TRACE(KC_A1_PENCIL);
+    int g = 0;
+    SphereArgs sa = E.sphere_args(pk, m, &g);
+    sa.c = o->c;
+    sa.ldc = o->ld;
+    sa.nreal = n;
+    FX_HIP(launch_sphere<T>(SPHERE_INV_PACK, P.n[0], sa, g, s));
   }
-  if ((st = E.transform(pk, m, +1)) != FOCK_OK) return st;
+  if ((st = E.plane_sphere(PLANE_INV, pk, m)) != FOCK_OK) return st;
   {
     FX_TRACE_S(KC_ZERO);
     FX_HIP(launch_zero<T>(acc, P.N * m, s));
@@ -1009,7 +1140,13 @@ fock_status apply_gamma_impl(const fock_cell* cell, const Plan& P, const fock_or
       }
     }
   }
-  if ((st = E.transform(acc, m, -1)) != FOCK_OK) return st;
+  if ((st = E.plane_sphere(PLANE_FWD, acc, m)) != FOCK_OK) return st;
+  {
+    FX_TRACE(KC_A7_PENCIL);
+    int g = 0;
+    const SphereArgs sa = E.sphere_args(acc, m, &g);
+    FX_HIP(launch_sphere<T>(SPHERE_FWD_BOX, P.n[0], sa, g, s));
+  }
   FX_TRACE(KC_A7_GATHER);
   FX_HIP(launch_gather_unpack<T>(acc, P.N, P.d_slot, P.npw, P.n, n, out, o->ld, s0, s));
   return FOCK_OK;
@@ -1353,6 +1490,55 @@ fock_status band_prepare(const fock_cell* cell, int32_t dtype, const fock_orbs* 
   return get_plan(cell, dtype, plan);
 }
 
+// Bands per chunk of launches: the live columns of its boxes, written by one
+// pass and read by the next, are the size of the 256 MB last-level cache.
+// Density and force of 128 bands on 96 x 96 x 128 FP64 with 64, 128, 256 and
+// 512 MB: 1166, 931, 815, 875 and 2022, 1759, 1561, 1655 us (less is in cache
+// above, more launches below).
+constexpr long long kBandCacheBytes = 256ll << 20;
+template <typename T>
+int band_chunk(const Plan& P, int cap, int nb) {
+  const long long per = (long long)P.n[0] * P.n[1] * P.sph.nc * 8 * (long long)sizeof(cx<T>);
+  const int n = (int)std::min<long long>(cap, std::max<long long>(1, kBandCacheBytes / std::max<long long>(1, per)));
+  return balanced_edge(nb, n);
+}
+
+// The passes of one chunk of bands up to the rows: coefficients -> columns
+// along i1 -> every row along i2.
+template <typename T>
+fock_status band_columns(Engine<T>& E, const fock_orbs* o, int b0, int n, void* box) {
+  const Plan& P = E.P;
+  hipStream_t s = E.s;
+  {
+    FX_TRACE(KC_A1_PENCIL);
+    int g = 0;
+    SphereArgs sa = E.sphere_args(box, n, &g);
+    sa.c = static_cast<const char*>(o->c) + (size_t)b0 * o->ld * sizeof(cx<T>);
+    sa.ldc = o->ld;
+    FX_HIP(launch_sphere<T>(SPHERE_INV, P.n[0], sa, g, s));
+  }
+  FX_TRACE(KC_A1_PLANE);
+  const Axis2Args xa{P.sph, box, P.d_tw[1], (P.sph.nc + 1) / 2};
+  FX_HIP(launch_axis2<T>(+1, P.n[1], P.n[2], xa, n * P.n[0] * xa.ngrp, s));
+  return FOCK_OK;
+}
+
+// blocks: workgroups wanted.  The density adds each group's partial sums to
+// memory once a chunk, so it takes 2048 (96 x 96 x 128 FP64, 128 bands, with
+// 1024, 2048 and 4096: 819, 781, 807 us), the force 4096 (1685, 1579, 1557).
+template <typename T>
+RowsArgs rows_args(const Plan& P, void* box, int n, int blocks, int most) {
+  RowsArgs ra{};
+  ra.tab = P.sph;
+  ra.box = box;
+  ra.tw3 = P.d_tw[2];
+  ra.N = P.N;
+  ra.nrb = P.n[0] * P.n[1] / rows_tune(P.n[2]).rb;
+  ra.nb = n;
+  ra.ngrp = std::min({most, n, (blocks + ra.nrb - 1) / ra.nrb});
+  return ra;
+}
+
 // rho[r] = sum_b w_b |psi_b(r)|^2, psi_b(r) = Omega^{-1/2} sum_G c_b(G) e^{iG.r}
 template <typename T>
 fock_status band_density_impl(const Plan& P, const fock_orbs* o, double* rho, char* ws, const BandLayout& L,
@@ -1360,39 +1546,24 @@ fock_status band_density_impl(const Plan& P, const fock_orbs* o, double* rho, ch
   Engine<T> E(P, s);
   void* box = ws + L.box;
   double* part = reinterpret_cast<double*>(ws + L.part);
-  for (int b0 = 0; b0 < o->nb; b0 += L.cb) {
-    const int n = std::min(L.cb, o->nb - b0);
-    const char* c = static_cast<const char*>(o->c) + (size_t)b0 * o->ld * sizeof(cx<T>);
-    {
-      FX_TRACE(KC_A1_SCATTER);
-      FX_HIP(launch_zero<T>(box, P.N * n, s));
-      FX_HIP(launch_scatter<T>(c, o->ld, P.d_slot, P.npw, n, box, P.N, s));
-    }
-    PencilArgs pa{};
-    pa.x = box;
-    pa.tw1 = P.d_tw[0];
-    pa.N = P.N;
-    pa.n2 = P.n[1];
-    pa.n3 = P.n[2];
-    pa.count = n;
-    { FX_TRACE(KC_A1_PENCIL); FX_HIP(launch_pencil<T>(PENCIL_INV, P.n[0], pa, n * E.ngroups, s)); }
-    PlaneArgs la{};
-    la.x = box;
-    la.tw2 = P.d_tw[1];
-    la.tw3 = P.d_tw[2];
-    la.N = P.N;
-    la.n1 = P.n[0];
-    la.nb = n;
-    la.f = o->w;
-    la.i0 = b0;
-    la.fscale = 1.0 / P.omega;
-    la.ngrp = kBandGroups;
-    la.part = part;
-    la.accumulate = b0 > 0;
-    { FX_TRACE(KC_BAND_DENS); FX_HIP(launch_plane<T>(PLANE_DENS, P.n[1], P.n[2], la, P.n[0] * kBandGroups, s)); }
+  const int chunk = band_chunk<T>(P, L.cb, o->nb);
+  int ngrp = 0;
+  for (int b0 = 0; b0 < o->nb; b0 += chunk) {
+    const int n = std::min(chunk, o->nb - b0);
+    const fock_status st = band_columns<T>(E, o, b0, n, box);
+    if (st != FOCK_OK) return st;
+    RowsArgs ra = rows_args<T>(P, box, n, 2048, kBandGroups);
+    if (b0 == 0) ngrp = ra.ngrp;
+    ra.ngrp = ngrp;
+    ra.f = o->w + b0;
+    ra.fscale = 1.0 / P.omega;
+    ra.part = part;
+    ra.accumulate = b0 > 0;
+    FX_TRACE(KC_BAND_DENS);
+    FX_HIP(launch_rows<T>(ROWS_DENS, P.n[2], ra, ra.nrb * ra.ngrp, s));
   }
   FX_TRACE(KC_REDUCE);
-  FX_HIP(launch_group_sum(part, o->nb > 0 ? kBandGroups : 0, P.N, rho, s));
+  FX_HIP(launch_group_sum(part, ngrp, P.N, rho, s));
   return FOCK_OK;
 }
 
@@ -1403,50 +1574,28 @@ fock_status band_force_impl(const Plan& P, const double k[3], const fock_orbs* o
                             char* ws, const BandLayout& L, hipStream_t s) {
   Engine<T> E(P, s);
   void* box = ws + L.box;
-  for (int b0 = 0; b0 < o->nb; b0 += L.cb) {
-    const int n = std::min(L.cb, o->nb - b0);
-    const char* c = static_cast<const char*>(o->c) + (size_t)b0 * o->ld * sizeof(cx<T>);
-    {
-      FX_TRACE(KC_A1_SCATTER);
-      FX_HIP(launch_zero<T>(box, P.N * n, s));
-      FX_HIP(launch_scatter<T>(c, o->ld, P.d_slot, P.npw, n, box, P.N, s));
-    }
-    PencilArgs pa{};
-    pa.x = box;
-    pa.tw1 = P.d_tw[0];
-    pa.N = P.N;
-    pa.n2 = P.n[1];
-    pa.n3 = P.n[2];
-    pa.count = n;
-    { FX_TRACE(KC_A1_PENCIL); FX_HIP(launch_pencil<T>(PENCIL_INV, P.n[0], pa, n * E.ngroups, s)); }
-    PlaneArgs la{};
-    la.x = box;
-    la.tw2 = P.d_tw[1];
-    la.tw3 = P.d_tw[2];
-    la.N = P.N;
-    la.n1 = P.n[0];
-    la.nb = n;
-    la.ngrp = kBandGroups;
-    la.vloc = vloc;
-    { FX_TRACE(KC_BAND_VMUL); FX_HIP(launch_plane<T>(PLANE_VMUL, P.n[1], P.n[2], la, P.n[0] * kBandGroups, s)); }
-    { FX_TRACE(KC_A7_PENCIL); FX_HIP(launch_pencil<T>(PENCIL_FWD, P.n[0], pa, n * E.ngroups, s)); }
-    ForceArgs fa{};
-    fa.box = box;
-    fa.N = P.N;
-    fa.slot = P.d_slot;
-    fa.npw = P.npw;
-    fa.c = o->c;
-    fa.ldc = o->ld;
-    fa.out = out;
-    fa.ldo = o->ld;
-    fa.w = o->w;
-    fa.j0 = b0;
-    std::memcpy(fa.b, P.b, sizeof(fa.b));
-    for (int a = 0; a < 3; ++a) fa.k[a] = k[a];
-    fa.n1 = P.n[0];
-    fa.n2 = P.n[1];
-    fa.n3 = P.n[2];
-    { FX_TRACE(KC_BAND_GATHER); FX_HIP(launch_force_gather<T>(fa, n, s)); }
+  const int chunk = band_chunk<T>(P, L.cb, o->nb);
+  for (int b0 = 0; b0 < o->nb; b0 += chunk) {
+    const int n = std::min(chunk, o->nb - b0);
+    const fock_status st = band_columns<T>(E, o, b0, n, box);
+    if (st != FOCK_OK) return st;
+    RowsArgs ra = rows_args<T>(P, box, n, 4096, n);
+    ra.vloc = vloc;
+    { FX_TRACE(KC_BAND_VMUL); FX_HIP(launch_rows<T>(ROWS_VMUL, P.n[2], ra, ra.nrb * ra.ngrp, s)); }
+    const Axis2Args xa{P.sph, box, P.d_tw[1], (P.sph.nc + 1) / 2};
+    { FX_TRACE(KC_A7_PLANE); FX_HIP(launch_axis2<T>(-1, P.n[1], P.n[2], xa, n * P.n[0] * xa.ngrp, s)); }
+    int g = 0;
+    SphereArgs sa = E.sphere_args(box, n, &g);
+    sa.c = o->c;
+    sa.ldc = o->ld;
+    sa.out = out;
+    sa.ldo = o->ld;
+    sa.w = o->w;
+    sa.j0 = b0;
+    std::memcpy(sa.b, P.b, sizeof(sa.b));
+    for (int a = 0; a < 3; ++a) sa.k[a] = k[a];
+    FX_TRACE(KC_A7_PENCIL);
+    FX_HIP(launch_sphere<T>(SPHERE_FORCE, P.n[0], sa, g, s));
   }
   return FOCK_OK;
 }

@@ -31,8 +31,6 @@ enum PlaneMode : int {
   PLANE_FWD = 2,       // in place, forward (a7)
   PLANE_INV = 3,       // in place, backward (a1)
   PLANE_INV_MAC_MIR = 4,  // P3, mirrored half of the pair-symmetric schedule
-  PLANE_DENS = 5,      // band loop: backward plane FFT, accumulate w |psi|^2
-  PLANE_VMUL = 6,      // band loop, in place: backward plane FFT, x V(r), forward plane FFT
   // Gamma point, real orbitals packed two per complex array (P_q = psi_2q + i psi_2q+1)
   PLANE_PAIR_FWD_G = 7,    // P1: phi_i(r) P_q(r), forward plane FFT
   PLANE_INV_MAC_G = 8,     // P3 into the packed targets' accumulators
@@ -68,22 +66,27 @@ struct PlaneArgs {
   int n1, nb;
   double fscale;       // constant factor on f in P3
   int store_v;         // P3: also write the real-space v back into the pair buffer
-  // band loops (PLANE_DENS, PLANE_VMUL): workgroup (i1, group g) takes the
-  // bands g, g + ngrp, ... < nb of x
-  int ngrp;
-  double* part;        // PLANE_DENS: FP64 partial densities [ngrp][N]
-  int accumulate;      // PLANE_DENS: add to part (else overwrite)
-  const void* vloc;    // PLANE_VMUL: real potential V(r) [N], path precision
   int nreal;           // Gamma modes: number of real orbitals (packed arrays hold ceil(nreal / 2))
   int tri;             // diagonal tile of a self-application (i0 == j0, ti == tj): only the
                        // pairs ii <= jj, pair buffer slot tri_slot(ii, jj)
-  const signed char* live;  // pair-buffer planes: per column i3 the last live row
-                            // (live_row); null: every entry is live
+  const signed char* live;  // per column i3 the last live row (live_row): of a pair
+                            // density, or of the sphere (PLANE_INV after and PLANE_FWD
+                            // before the sphere pencils); null: every entry is live
 };
 
 // Row i2 of plane column with bound h (|m2| <= h, h < 0: empty column) holds
 // pair-density data; entries outside are zero and are neither stored nor read.
 template <int N2> __device__ __forceinline__ bool live_row(int i2, int h) { return i2 <= h || i2 >= N2 - h; }
+
+// Whether the 128-byte line that lane t stores to at row i2 holds a live
+// entry: the lanes of an aligned lane group of one line hold consecutive
+// columns (rows that do not start on a line give groups of half lines, which
+// only moves the rounding).
+template <typename T, int N2> __device__ __forceinline__ bool live_line(int i2, int h, int t) {
+  constexpr int LINE = 128 / (int)sizeof(cx<T>);
+  const unsigned long long m = __ballot(live_row<N2>(i2, h));
+  return ((m >> ((t & 63) & ~(LINE - 1))) & ((1ull << LINE) - 1)) != 0;
+}
 
 // How P1 walks a tile and stores its partly live lines.
 // strip: the workgroups of one plane take `strip` occupied orbitals at a time
@@ -226,10 +229,9 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
   // the rows with its lanes: the forward direction's second row pass, the
   // backward direction's first.  Its exchanges then spread the lanes of a
   // wave over 32 rows at the odd stride COLS + 1, one bank pair each,
-  // instead of over strided columns of a few rows.  The V-multiply mode,
-  // whose row passes also meet V(r) in HBM, keeps the default order.
+  // instead of over strided columns of a few rows.
   constexpr bool fwd_dir = MODE == PLANE_PAIR_FWD || MODE == PLANE_PAIR_FWD_G || MODE == PLANE_FWD;
-  constexpr bool rows_lb = !PAD && MODE != PLANE_VMUL;
+  constexpr bool rows_lb = !PAD;
   using R0 = std::conditional_t<rows_lb && !fwd_dir, typename Cfg::Rw::P0b, typename Cfg::Rw::P0>;
   using R1 = std::conditional_t<rows_lb && fwd_dir, typename Cfg::Rw::P1b, typename Cfg::Rw::P1>;
   using C0 = typename Cfg::Cl::P0;
@@ -299,16 +301,10 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     cx<T>* pw = reinterpret_cast<cx<T>*>(A.w) + (long long)slot * N + (long long)i1 * PLANE;
     // Dead entries are not stored, or (P1Tune::lines) a 128-byte line with a
     // live entry is written whole: the dead entries' values are never read.
-    // The LINE lanes of an aligned lane group hold consecutive columns.
-    constexpr int LINE = 128 / (int)sizeof(cx<T>);
     for_outputs<C1>(t, [&](int e, int row, int col) {
-      bool st = live_row<N2>(row, hc);
-      if constexpr (p1_tune(sizeof(T), N2, N3, gam).lines) {
-        if (A.live) {
-          const unsigned long long m = __ballot(st);
-          st = ((m >> ((t & 63) & ~(LINE - 1))) & ((1ull << LINE) - 1)) != 0;
-        }
-      }
+      bool st;
+      if constexpr (p1_tune(sizeof(T), N2, N3, gam).lines) st = live_line<T, N2>(row, hc, t);
+      else st = live_row<N2>(row, hc);
       if (st) store_stream<T>(&pw[row * N3 + col], v[e]);
     });
   } else if constexpr (MODE == PLANE_INV_MAC || MODE == PLANE_INV_MAC_MIR) {
@@ -448,63 +444,11 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     pass_compute<C0, -1, T>(v, tw2, t);
     exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
     pass_compute<C1, -1, T>(v, tw2, t);
-    for_outputs<C1>(t, [&](int e, int row, int col) { px[row * N3 + col] = v[e]; });
-  } else if constexpr (MODE == PLANE_DENS) {
-    stage();
-    // sum over this group's bands of f_b * fscale * |psi_b(r)|^2 on plane i1
-    const int G = A.ngrp;
-    const int i1 = lid / G, g = lid - (lid / G) * G;
-    T acc[R1::NV];
-#pragma unroll
-    for (int e = 0; e < R1::NV; ++e) acc[e] = T(0);
-    for (int b = g; b < A.nb; b += G) {
-      const cx<T>* px = reinterpret_cast<const cx<T>*>(A.x) + (long long)b * N + (long long)i1 * PLANE;
-      for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = px[row * N3 + col]; });
-      pass_compute<C0, +1, T>(v, tw2, t);
-      exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<C1, +1, T>(v, tw2, t);
-      exchange<C1, R0, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<R0, +1, T>(v, tw3, t);
-      exchange<R0, R1, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<R1, +1, T>(v, tw3, t);
-      const T wb = T(A.f[A.i0 + b] * A.fscale);
-      for_outputs<R1>(t, [&](int e, int row, int col) { acc[e] += wb * (v[e].x * v[e].x + v[e].y * v[e].y); });
-    }
-    double* pp = A.part + (long long)g * N + (long long)i1 * PLANE;
-    for_outputs<R1>(t, [&](int e, int row, int col) {
-      const int p = row * N3 + col;
-      pp[p] = (A.accumulate ? pp[p] : 0.0) + double(acc[e]);
+    // live (sphere columns): only the lines the sphere pencils read are stored
+    const int hc = A.live ? A.live[t % N3] : N2;
+    for_outputs<C1>(t, [&](int e, int row, int col) {
+      if (live_line<T, N2>(row, hc, t)) px[row * N3 + col] = v[e];
     });
-  } else if constexpr (MODE == PLANE_VMUL) {
-    // psi_b(i1, r2, r3) = backward plane FFT; times V(r); forward plane FFT
-    // back into place.  V's plane stays in registers for the group's bands.
-    const int G = A.ngrp;
-    const int i1 = lid / G, g = lid - (lid / G) * G;
-    stage();
-    const T* pv = reinterpret_cast<const T*>(A.vloc) + (long long)i1 * PLANE;
-    T vr[R1::NV];
-    for_outputs<R1>(t, [&](int e, int row, int col) { vr[e] = pv[row * N3 + col]; });
-    for (int b = g; b < A.nb; b += G) {
-      cx<T>* px = reinterpret_cast<cx<T>*>(A.x) + (long long)b * N + (long long)i1 * PLANE;
-      for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = px[row * N3 + col]; });
-      pass_compute<C0, +1, T>(v, tw2, t);
-      exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<C1, +1, T>(v, tw2, t);
-      exchange<C1, R0, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<R0, +1, T>(v, tw3, t);
-      exchange<R0, R1, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<R1, +1, T>(v, tw3, t);
-      for_outputs<R1>(t, [&](int e, int row, int col) { v[e] = cscale<T>(v[e], vr[e]); });
-      exchange<R1, R0, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<R0, -1, T>(v, tw3, t);
-      exchange<R0, R1, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<R1, -1, T>(v, tw3, t);
-      exchange<R1, C0, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<C0, -1, T>(v, tw2, t);
-      exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
-      pass_compute<C1, -1, T>(v, tw2, t);
-      for_outputs<C1>(t, [&](int e, int row, int col) { px[row * N3 + col] = v[e]; });
-    }
   } else {  // PLANE_INV
     const int ob = lid / A.n1, i1 = lid - (lid / A.n1) * A.n1;
     cx<T>* px = reinterpret_cast<cx<T>*>(A.x) + (long long)ob * N + (long long)i1 * PLANE;
@@ -537,11 +481,8 @@ constexpr PlaneTune plane_tune(int tbytes, int n2, int n3, int mode) {
              pair = p1 || inv,
              fwdmac = mode == PLANE_INV_MAC || mode == PLANE_INV_MAC_G,
              mirror = mode == PLANE_INV_MAC_MIR || mode == PLANE_INV_MAC_MIR_G,
-             mac = fwdmac || mirror || mode == PLANE_DENS;
-  // band loops hold an accumulator or V(r) in registers beside the plane
-  const bool band = mode == PLANE_DENS || mode == PLANE_VMUL;
+             mac = fwdmac || mirror;
   if (tbytes == 8) {  // FP64
-    if (band && n2 == 96 && n3 == 128) return PlaneTune{768, true, 1};
     if (n2 == 64 && n3 == 64) {
       if (p1) return PlaneTune{512, true, 1};
       if (inv) return PlaneTune{512, true, 2};
@@ -992,22 +933,6 @@ __global__ void gather_kernel(const cx<T>* __restrict__ box, long long N, const 
     out[(long long)j * ldo + p] = cscale<T>(box[(long long)j * N + slot[p]], st);
 }
 
-// Gamma packing of real orbitals: box[q][slot[p]] = c[2q][p] + i c[2q+1][p]
-// (the second row is absent for the last q of an odd count).
-template <typename T>
-__global__ void scatter_pack_kernel(const cx<T>* __restrict__ c, int ldc, const int* __restrict__ slot, int npw,
-                                    int nreal, cx<T>* __restrict__ box, long long N) {
-  const int q = blockIdx.y;
-  const bool two = 2 * q + 1 < nreal;
-  const cx<T>* c0 = c + (long long)(2 * q) * ldc;
-  const cx<T>* c1 = c0 + ldc;
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < npw; p += gridDim.x * blockDim.x) {
-    const cx<T> a = c0[p];
-    const cx<T> b = two ? c1[p] : mk<T>(T(0), T(0));
-    box[(long long)q * N + slot[p]] = mk<T>(a.x - b.y, a.y + b.x);
-  }
-}
-
 // Unpack the transform F = FFT[acc_2q + i acc_2q+1] of two real functions on
 // the sphere: FFT[acc_2q](G) = (F(G) + conj F(-G)) / 2 and
 // FFT[acc_2q+1](G) = (F(G) - conj F(-G)) / (2i); rows 2q and 2q+1 of out,
@@ -1051,49 +976,6 @@ __global__ void band_dot_kernel(const cx<T>* __restrict__ c, int ldc, const cx<T
   }
   const double tot = block_sum(s, red);
   if (threadIdx.x == 0) part[b] = g ? g[b] * tot : tot;
-}
-
-// Band force on the sphere:
-//   out[j][p] = -w[j0+j] * (1/2 |k+G_p|^2 c[j][p] + box[j][slot[p]] / N)
-struct ForceArgs {
-  const void* box;     // [nj][N]: FFT[V psi_j], unnormalised
-  long long N;
-  const int* slot;
-  int npw;
-  const void* c;       // [*][ldc] sphere coefficients (row j0 + j)
-  int ldc;
-  void* out;           // [*][ldo] (row j0 + j)
-  int ldo;
-  const double* w;
-  int j0;
-  double b[3][3];      // reciprocal vectors (rows)
-  double k[3];
-  int n1, n2, n3;
-};
-
-template <typename T>
-__global__ void force_gather_kernel(ForceArgs A) {
-  const int j = blockIdx.y;
-  const double wj = A.w[A.j0 + j];
-  const cx<T>* box = reinterpret_cast<const cx<T>*>(A.box) + (long long)j * A.N;
-  const cx<T>* c = reinterpret_cast<const cx<T>*>(A.c) + (long long)(A.j0 + j) * A.ldc;
-  cx<T>* out = reinterpret_cast<cx<T>*>(A.out) + (long long)(A.j0 + j) * A.ldo;
-  const double inv_n = 1.0 / double(A.N);
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < A.npw; p += gridDim.x * blockDim.x) {
-    const int s = A.slot[p];
-    const int i3 = s % A.n3, i12 = s / A.n3;
-    const int i2 = i12 % A.n2, i1 = i12 / A.n2;
-    const int m1 = signed_index(i1, A.n1), m2 = signed_index(i2, A.n2), m3 = signed_index(i3, A.n3);
-    double g2 = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double ga = A.k[a] + m1 * A.b[0][a] + m2 * A.b[1][a] + m3 * A.b[2][a];
-      g2 += ga * ga;
-    }
-    const cx<T> v = box[s], cp = c[p];
-    const T kin = T(0.5 * g2), sv = T(inv_n), mw = T(-wj);
-    out[p] = mk<T>(mw * (kin * cp.x + sv * v.x), mw * (kin * cp.y + sv * v.y));
-  }
 }
 
 }  // namespace fockx

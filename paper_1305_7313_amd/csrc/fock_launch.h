@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "fock_kernels.h"
+#include "sphere_kernels.h"
 #include "batch_kernel.h"
 
 namespace fockx {
@@ -24,16 +25,15 @@ hipError_t launch_gather(const void* box, long long N, const int* slot, int npw,
                          const double* w, int j0, const double* g, hipStream_t s);
 
 template <typename T>
-hipError_t launch_scatter_pack(const void* c, int ldc, const int* slot, int npw, int nreal, void* box, long long N,
-                               hipStream_t s);
-template <typename T>
 hipError_t launch_gather_unpack(const void* box, long long N, const int* slot, int npw, const int n[3], int nreal,
                                 void* out, int ldo, double s0, hipStream_t s);
 template <typename T> hipError_t launch_mac_gamma(const MacArgs& a, int nreal, hipStream_t s);
 template <typename T>
 hipError_t launch_band_dot(const void* c, int ldc, const void* v, int ldv, int npw, const double* g, int nb,
                            double* part, hipStream_t s);
-template <typename T> hipError_t launch_force_gather(const ForceArgs& a, int nj, hipStream_t s);
+template <typename T> hipError_t launch_sphere(int mode, int n1, const SphereArgs& a, int nblocks, hipStream_t s);
+template <typename T> hipError_t launch_axis2(int dir, int n2, int n3, const Axis2Args& a, int nblocks, hipStream_t s);
+template <typename T> hipError_t launch_rows(int mode, int n3, const RowsArgs& a, int nblocks, hipStream_t s);
 hipError_t launch_group_sum(const double* part, int ngrp, long long N, double* rho, hipStream_t s);
 
 hipError_t launch_energy_tile(const double* epart, int ngroups, const double* f, const double* g, int i0, int j0, int ti,

@@ -19,8 +19,6 @@ hipError_t plane_mode(int mode, const PlaneArgs& a, int nblocks, hipStream_t s) 
     case PLANE_FWD: return plane_go<PLANE_FWD, N2, N3>(a, nblocks, s);
     case PLANE_INV: return plane_go<PLANE_INV, N2, N3>(a, nblocks, s);
     case PLANE_INV_MAC_MIR: return plane_go<PLANE_INV_MAC_MIR, N2, N3>(a, nblocks, s);
-    case PLANE_DENS: return plane_go<PLANE_DENS, N2, N3>(a, nblocks, s);
-    case PLANE_VMUL: return plane_go<PLANE_VMUL, N2, N3>(a, nblocks, s);
     case PLANE_PAIR_FWD_G: return plane_go<PLANE_PAIR_FWD_G, N2, N3>(a, nblocks, s);
     case PLANE_INV_MAC_G: return plane_go<PLANE_INV_MAC_G, N2, N3>(a, nblocks, s);
     case PLANE_INV_MAC_MIR_G: return plane_go<PLANE_INV_MAC_MIR_G, N2, N3>(a, nblocks, s);
@@ -135,16 +133,6 @@ hipError_t launch_gather<FX_T>(const void* box, long long N, const int* slot, in
 }
 
 template <>
-hipError_t launch_scatter_pack<FX_T>(const void* c, int ldc, const int* slot, int npw, int nreal, void* box,
-                                     long long N, hipStream_t s) {
-  const int m = (nreal + 1) / 2;
-  if (m <= 0 || npw <= 0) return hipSuccess;
-  hipLaunchKernelGGL(scatter_pack_kernel<FX_T>, dim3((npw + 255) / 256, m), dim3(256), 0, s,
-                     reinterpret_cast<const cx<FX_T>*>(c), ldc, slot, npw, nreal, reinterpret_cast<cx<FX_T>*>(box), N);
-  return hipGetLastError();
-}
-
-template <>
 hipError_t launch_gather_unpack<FX_T>(const void* box, long long N, const int* slot, int npw, const int n[3],
                                       int nreal, void* out, int ldo, double s0, hipStream_t s) {
   const int m = (nreal + 1) / 2;
@@ -171,12 +159,84 @@ hipError_t launch_band_dot<FX_T>(const void* c, int ldc, const void* v, int ldv,
   return hipGetLastError();
 }
 
-template <>
-hipError_t launch_force_gather<FX_T>(const ForceArgs& a, int nj, hipStream_t s) {
-  if (nj <= 0 || a.npw <= 0) return hipSuccess;
-  const int bx = (a.npw + 255) / 256;
-  hipLaunchKernelGGL(force_gather_kernel<FX_T>, dim3(bx, nj), dim3(256), 0, s, a);
+namespace {
+template <int MODE, int N1>
+hipError_t sphere_go(const SphereArgs& a, int nblocks, hipStream_t s) {
+  using C = PencilCfg<FX_T, N1, PENCIL_INV>;
+  hipLaunchKernelGGL((sphere_kernel<FX_T, N1, C::CB, C::W, C::SPLIT, MODE>), dim3(nblocks), dim3(C::W), 0, s, a);
   return hipGetLastError();
+}
+template <int N1>
+hipError_t sphere_mode(int mode, const SphereArgs& a, int nblocks, hipStream_t s) {
+  switch (mode) {
+    case SPHERE_INV: return sphere_go<SPHERE_INV, N1>(a, nblocks, s);
+    case SPHERE_INV_PACK: return sphere_go<SPHERE_INV_PACK, N1>(a, nblocks, s);
+    case SPHERE_FWD: return sphere_go<SPHERE_FWD, N1>(a, nblocks, s);
+    case SPHERE_FWD_BOX: return sphere_go<SPHERE_FWD_BOX, N1>(a, nblocks, s);
+    case SPHERE_FORCE: return sphere_go<SPHERE_FORCE, N1>(a, nblocks, s);
+  }
+  return hipErrorInvalidValue;
+}
+template <int N2, int N3>
+hipError_t axis2_go(int dir, const Axis2Args& a, int nblocks, hipStream_t s) {
+  if (dir > 0)
+    hipLaunchKernelGGL((axis2_kernel<FX_T, N2, N3, +1>), dim3(nblocks), dim3(axis2_threads(N2)), 0, s, a);
+  else
+    hipLaunchKernelGGL((axis2_kernel<FX_T, N2, N3, -1>), dim3(nblocks), dim3(axis2_threads(N2)), 0, s, a);
+  return hipGetLastError();
+}
+template <int N3>
+hipError_t rows_go(int mode, const RowsArgs& a, int nblocks, hipStream_t s) {
+  if (mode == ROWS_DENS)
+    hipLaunchKernelGGL((rows_kernel<FX_T, N3, ROWS_DENS>), dim3(nblocks), dim3(rows_tune(N3).w), 0, s, a);
+  else
+    hipLaunchKernelGGL((rows_kernel<FX_T, N3, ROWS_VMUL>), dim3(nblocks), dim3(rows_tune(N3).w), 0, s, a);
+  return hipGetLastError();
+}
+}  // namespace
+
+template <>
+hipError_t launch_sphere<FX_T>(int mode, int n1, const SphereArgs& a, int nblocks, hipStream_t s) {
+  if (nblocks <= 0) return hipSuccess;
+  switch (n1) {
+    case 24: return sphere_mode<24>(mode, a, nblocks, s);
+    case 48: return sphere_mode<48>(mode, a, nblocks, s);
+    case 64: return sphere_mode<64>(mode, a, nblocks, s);
+    case 72: return sphere_mode<72>(mode, a, nblocks, s);
+    case 96: return sphere_mode<96>(mode, a, nblocks, s);
+    case 128: return sphere_mode<128>(mode, a, nblocks, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <>
+hipError_t launch_axis2<FX_T>(int dir, int n2, int n3, const Axis2Args& a, int nblocks, hipStream_t s) {
+  if (nblocks <= 0) return hipSuccess;
+#define FX_AXIS2(A, B) \
+  if (n2 == A && n3 == B) return axis2_go<A, B>(dir, a, nblocks, s);
+  FX_AXIS2(24, 24)
+  FX_AXIS2(48, 48)
+  FX_AXIS2(48, 64)
+  FX_AXIS2(64, 64)
+  FX_AXIS2(72, 72)
+  FX_AXIS2(96, 96)
+  FX_AXIS2(96, 128)
+#undef FX_AXIS2
+  return hipErrorInvalidValue;
+}
+
+template <>
+hipError_t launch_rows<FX_T>(int mode, int n3, const RowsArgs& a, int nblocks, hipStream_t s) {
+  if (nblocks <= 0) return hipSuccess;
+  switch (n3) {
+    case 24: return rows_go<24>(mode, a, nblocks, s);
+    case 48: return rows_go<48>(mode, a, nblocks, s);
+    case 64: return rows_go<64>(mode, a, nblocks, s);
+    case 72: return rows_go<72>(mode, a, nblocks, s);
+    case 96: return rows_go<96>(mode, a, nblocks, s);
+    case 128: return rows_go<128>(mode, a, nblocks, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace fockx

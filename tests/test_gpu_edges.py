@@ -36,3 +36,71 @@ def test_pair_pass_strips(n, prec, nocc, ntgt):
     e, er = rel_fro(v, ref), max_row_rel(v, ref)
     report(f"strips {n} {prec} {nocc}x{ntgt}", rel=e, maxband=er)
     assert e < TOL[prec] and er < TOL[prec]
+
+
+def _sphere(n, kind):
+    """A system on grid n whose plane-wave list is the full sphere in random
+    order, a ragged part of it (not symmetric, columns missing), or G = 0 alone."""
+    s = synth.make_system(synth.ortho_cell(*(x / 4.0 for x in n)), n)
+    rng = np.random.default_rng(5)
+    m = s.miller[rng.permutation(s.npw)]
+    if kind == "ragged":
+        m = m[(m[:, 1] > -3) & (m[:, 2] % 3 != 1)]
+    elif kind == "one":
+        m = np.zeros((1, 3), dtype=np.int32)
+    s.miller = np.ascontiguousarray(m)
+    return s
+
+
+SPHERES = [((24, 24, 24), "full"), ((48, 48, 64), "full"), ((64, 64, 64), "ragged"), ((72, 72, 72), "full"),
+           ((96, 96, 96), "ragged"), ((128, 96, 128), "full"), ((72, 48, 48), "ragged"), ((24, 72, 72), "one")]
+
+
+# sphere passes and the band loops' one-dimensional passes on every line length,
+# with plane waves in any order
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("n,kind", SPHERES)
+def test_sphere_passes(n, kind, prec):
+    import torch
+    from oracle import bands
+    from paper_1305_7313_amd import fock as F
+    s = _sphere(n, kind)
+    rng = np.random.default_rng(6)
+    nb = 3
+    c = rng.standard_normal((nb, s.npw)) + 1j * rng.standard_normal((nb, s.npw))
+    c /= np.linalg.norm(c, axis=1)[:, None]
+    w = np.array([2.0, 0.5, 1.25])
+    v, k = rng.standard_normal(n), np.array([0.07, -0.02, 0.05])
+    cell = F.Cell(s.a, s.n, s.miller)
+    cd, wd = dev(c, _dtype(prec)), dev(w)
+    print(f"[case] sphere {n} {kind} {prec}: {s.npw} plane waves", flush=True)
+    rho = host(F.fock_band_density(cell, cd, wd))
+    e1 = rel_fro(rho, bands.band_density(s.a, s.n, s.miller, c, w))
+    vd = dev(v, torch.float64 if prec == "c128" else torch.float32)
+    e2 = rel_fro(host(F.fock_band_force(cell, k, cd, wd, vd)), bands.band_force(s.a, s.n, s.miller, k, c, w, v))
+    q = np.array([0.03, 0.01, -0.02])
+    ref = exx.fock_apply(s.a, s.n, s.miller, q, c[:2], w[:2], c[2:])
+    e3 = rel_fro(host(F.fock_apply(cell, q, cd[:2], wd[:2], cd[2:])), ref)
+    report(f"sphere {n} {kind} {prec}", density=e1, force=e2, apply=e3)
+    assert max(e1, e2, e3) < TOL[prec]
+
+
+# bands around the chunk and group boundaries of the band loops
+@pytest.mark.parametrize("prec,nb", [("c128", 1), ("c128", 65), ("c64", 9), ("c64", 70)])
+def test_band_chunks(prec, nb):
+    import torch
+    from oracle import bands
+    from paper_1305_7313_amd import fock as F
+    s = synth.make_system(synth.cubic_cell(12.0), (48, 48, 48))
+    c = synth.random_orbitals(s.a, s.miller, nb, 3)
+    w = np.linspace(0.5, 2.0, nb)
+    v = np.random.default_rng(7).standard_normal(s.n)
+    cell = F.Cell(s.a, s.n, s.miller)
+    cd, wd = dev(c, _dtype(prec)), dev(w)
+    print(f"[case] band chunks {prec} {nb}", flush=True)
+    e1 = rel_fro(host(F.fock_band_density(cell, cd, wd)), bands.band_density(s.a, s.n, s.miller, c, w))
+    vd = dev(v, torch.float64 if prec == "c128" else torch.float32)
+    k = np.zeros(3)
+    e2 = rel_fro(host(F.fock_band_force(cell, k, cd, wd, vd)), bands.band_force(s.a, s.n, s.miller, k, c, w, v))
+    report(f"band chunks {prec} {nb}", density=e1, force=e2)
+    assert max(e1, e2) < TOL[prec]
