@@ -511,7 +511,11 @@ constexpr PlaneTune plane_tune(int tbytes, int n2, int n3, int mode) {
     // workgroups of 720 threads (12 waves) fit (16-system batch 1086 -> 1071
     // ms, 72^3 k-mesh 8723 -> 8246 ms)
     if (p1) return PlaneTune{504, false, 6};  // at most 80 registers, else two planes per CU
-    if (fwdmac || mirror) return PlaneTune{720, false, 1};
+    // the fused passes at no more than 80 registers: two workgroups per CU instead
+    // of one (45 x 21 orbitals at q != 0: 1291 -> 975 us, 64 x 32: 2821 -> 2215);
+    // the Gamma forms would spill under that bound
+    if (mode == PLANE_INV_MAC || mode == PLANE_INV_MAC_MIR) return PlaneTune{720, false, 6};
+    if (mac) return PlaneTune{720, false, 1};
     return inv ? PlaneTune{504, true, 1} : PlaneTune{576, false, 1};
   }
   if (n2 == 64 && n3 == 64) return p1 ? PlaneTune{256, true, 1} : PlaneTune{512, false, 1};
