@@ -185,7 +185,7 @@ def sym_schedule(fp64, n3):
     env = os.environ.get("FOCK_SYM_SCHEDULE")
     if env in ("0", "1", "2"):
         return int(env)
-    return 2 if fp64 and n3 <= 64 else 1
+    return 2 if n3 <= (64 if fp64 else 24) else 1
 
 
 def live_fraction(miller, n):

@@ -427,18 +427,24 @@ int balanced_edge(int n, int edge) {
   const int parts = (n + edge - 1) / edge;
   return (n + parts - 1) / parts;
 }
-Tiles tiles_for(int n_occ, int n_tgt, int cplx_bytes) {
-  const int edge = pair_tile(cplx_bytes);
-  Tiles t;
-  t.ti = balanced_edge(n_occ, edge);
-  t.tj = balanced_edge(n_tgt, edge);
-  return t;
-}
 // Workspace bounds for any job on blocks of up to nmax orbitals: no tile edge
 // exceeds min(nmax, edge) (the balanced edge is not monotonic in n), and a
 // block of n orbitals has ceil(n / edge) tiles along it.
 int tile_cap(int nmax, int cplx_bytes) { return std::max(1, std::min(nmax, pair_tile(cplx_bytes))); }
 int tile_count(int n, int cplx_bytes) { return n > 0 ? (n + pair_tile(cplx_bytes) - 1) / pair_tile(cplx_bytes) : 1; }
+
+// wide: the occupied side may exceed the edge where the target side is short,
+// up to the pairs a square tile holds (few targets against many orbitals: one
+// launch instead of several that leave the GPU half empty).  Not for the
+// streaming multiply-accumulate, whose threads hold one tile row of at most the
+// edge.
+Tiles tiles_for(int n_occ, int n_tgt, int cplx_bytes, bool wide) {
+  const int edge = pair_tile(cplx_bytes), tc = tile_cap(std::max(n_occ, n_tgt), cplx_bytes);
+  Tiles t;
+  t.tj = balanced_edge(n_tgt, edge);
+  t.ti = balanced_edge(n_occ, wide ? std::max(edge, tc * tc / t.tj) : edge);
+  return t;
+}
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -555,7 +561,7 @@ struct Engine {
 
   // Plane pass of orbitals, in place (PLANE_INV, PLANE_FWD): only the sphere's
   // columns are read or written on the reciprocal side.
-  fock_status plane_sphere(int mode, void* box, int nb) {
+  fock_status plane_sphere(int mode, void* box, int nb, int nsum = 1, void* box2 = nullptr, int nb2 = 0) {
     PlaneArgs la{};
     la.x = box;
     la.tw2 = P.d_tw[1];
@@ -564,9 +570,34 @@ struct Engine {
     la.n1 = P.n[0];
     la.nb = nb;
     la.live = P.sph.live;
+    la.split = nsum;
+    la.sstride = (long long)nb * P.N;
+    la.x2 = box2;
     FX_TRACE(mode == PLANE_INV ? KC_A1_PLANE : KC_A7_PLANE);
-    FX_HIP(launch_plane<T>(mode, P.n[1], P.n[2], la, nb * P.n[0], s));
+    FX_HIP(launch_plane<T>(mode, P.n[1], P.n[2], la, (nb + nb2) * P.n[0], s));
     return FOCK_OK;
+  }
+
+  // Two blocks in one launch per pass.
+  fock_status to_real_space2(const fock_orbs* a, void* boxa, const fock_orbs* b, void* boxb) {
+    fock_status st;
+    if (!P.d_sph || a->nb <= 0 || b->nb <= 0) {
+      if ((st = to_real_space(a->c, a->ld, a->nb, boxa)) != FOCK_OK) return st;
+      return to_real_space(b->c, b->ld, b->nb, boxb);
+    }
+    {
+      FX_TRACE(KC_A1_PENCIL);
+      int g = 0;
+      SphereArgs sa = sphere_args(boxa, a->nb + b->nb, &g);
+      sa.c = a->c;
+      sa.ldc = a->ld;
+      sa.box2 = boxb;
+      sa.c2 = b->c;
+      sa.ldc2 = b->ld;
+      sa.nb1 = a->nb;
+      FX_HIP(launch_sphere<T>(SPHERE_INV, P.n[0], sa, g, s));
+    }
+    return plane_sphere(PLANE_INV, boxa, a->nb, 1, boxb, b->nb);
   }
 
   fock_status to_real_space(const void* c, int ld, int nb, void* box) {
@@ -590,7 +621,8 @@ struct Engine {
     return transform(box, nb, +1);
   }
 
-  fock_status transform(void* box, int nb, int sign) {
+  // nsum > 1 (forward): box b is the sum of the boxes b, b + nb, ... b + (nsum - 1) nb.
+  fock_status transform(void* box, int nb, int sign, int nsum = 1) {
     PencilArgs pa{};
     pa.x = box;
     pa.tw1 = P.d_tw[0];
@@ -605,6 +637,8 @@ struct Engine {
     la.N = P.N;
     la.n1 = P.n[0];
     la.nb = nb;
+    la.split = nsum;
+    la.sstride = (long long)nb * P.N;
     if (sign > 0) {
       { FX_TRACE(KC_A1_PENCIL); FX_HIP(launch_pencil<T>(PENCIL_INV, P.n[0], pa, nb * ngroups, s)); }
       { FX_TRACE(KC_A1_PLANE); FX_HIP(launch_plane<T>(PLANE_INV, P.n[1], P.n[2], la, nb * P.n[0], s)); }
@@ -620,17 +654,14 @@ struct Engine {
     std::memcpy(kp.b, P.b, sizeof(kp.b));
     for (int k = 0; k < 3; ++k) kp.q[k] = q[k];
     kp.ecut = cell->ecut_fock;
-    kp.k0 = d_k0;
+    kp.k0 = cell->g0 == FOCK_G0_ZERO ? nullptr : d_k0;
     kp.q_zero = q_zero ? 1 : 0;
     return kp;
   }
 
-  // K at q + G = 0 into d_k0 (device FP64 scalar).
+  // K at q + G = 0 into d_k0 (device FP64 scalar), where it is not zero and used.
   fock_status g0_constant(const fock_cell* cell, bool q_zero, double* d_k0, double* d_part) {
-    if (!q_zero || cell->g0 == FOCK_G0_ZERO) {
-      FX_HIP(launch_set_scalar(d_k0, 0.0, s));
-      return FOCK_OK;
-    }
+    if (!q_zero || cell->g0 == FOCK_G0_ZERO) return FOCK_OK;
     KernelParams kp{};
     std::memcpy(kp.b, P.b, sizeof(kp.b));
     const int nqt = cell->nq[0] * cell->nq[1] * cell->nq[2];
@@ -690,13 +721,14 @@ struct Engine {
     return FOCK_OK;
   }
 
-  // acc[0..nj) (real space) -> forward FFT -> sphere rows j0.. of out, scaled.
+  // acc[0..nj) (real space; nsum partial sums, nj boxes apart) -> forward FFT ->
+  // sphere rows j0.. of out, scaled.
   fock_status finish(void* acc, int nj, int j0, void* out, int ldo, double s0, const double* wout,
-                     const double* gscale) {
+                     const double* gscale, int nsum = 1) {
     fock_status st;
     if (P.d_sph) {
       if (nj <= 0) return FOCK_OK;
-      if ((st = plane_sphere(PLANE_FWD, acc, nj)) != FOCK_OK) return st;
+      if ((st = plane_sphere(PLANE_FWD, acc, nj, nsum)) != FOCK_OK) return st;
       FX_TRACE(KC_A7_PENCIL);
       int g = 0;
       SphereArgs sa = sphere_args(acc, nj, &g);
@@ -709,7 +741,7 @@ struct Engine {
       FX_HIP(launch_sphere<T>(SPHERE_FWD, P.n[0], sa, g, s));
       return FOCK_OK;
     }
-    if ((st = transform(acc, nj, -1)) != FOCK_OK) return st;
+    if ((st = transform(acc, nj, -1, nsum)) != FOCK_OK) return st;
     char* o = static_cast<char*>(out) + (size_t)j0 * ldo * sizeof(cx<T>);
     FX_TRACE(KC_A7_GATHER);
     FX_HIP(launch_gather<T>(acc, P.N, P.d_slot, P.npw, nj, o, ldo, s0, wout, j0, gscale, s));
@@ -720,8 +752,9 @@ struct Engine {
   //   0  fused inverse FFT + MAC into acc_J, v_ij written back and streamed
   //      into acc_I by a second kernel;
   //   1  fully parallel in-place inverse FFT, then one MAC kernel for both
-  //      halves (default for FP32, whose transforms are VALU-bound, and for
-  //      FP64 planes from 72 points wide);
+  //      halves (default for FP32, whose transforms are VALU-bound, beyond 24
+  //      points: a 24^3 box gives the MAC's thread per point 54 workgroups, 64
+  //      orbitals 667 against 577 us; and for FP64 planes from 72 points wide);
   //   2  fused inverse FFT + MAC into acc_J, and a second fused pass that
   //      recomputes v_ij and accumulates the mirror into acc_I: no write-back,
   //      one more transform (default for FP64 planes up to 64 points wide,
@@ -734,7 +767,8 @@ struct Engine {
     const char* e = std::getenv("FOCK_SYM_SCHEDULE");
     const int env = e ? std::atoi(e) : -1;
     if (env >= 0 && env <= 2) return env;
-    return sizeof(T) == 8 && P.n[2] <= 64 ? 2 : 1;
+    if (sizeof(T) == 4) return P.n[2] <= 24 ? 2 : 1;
+    return P.n[2] <= 64 ? 2 : 1;
   }
 
   // Apply of an occupied block to a different target block (or at q != 0):
@@ -752,6 +786,15 @@ struct Engine {
     const int env = e ? std::atoi(e) : -1;
     if (env == 0 || env == 1) return env;
     return sizeof(T) == 8 && P.n[1] * P.n[2] > 96 * 96 ? 1 : 0;
+  }
+
+  // Parts of the fused pass's occupied loop.  Its grid has a workgroup per
+  // (target, plane); two run on a CU, so below 1024 the GPU drains half empty or
+  // does not fill (48^3 FP64, 40 x 5 orbitals: 240 workgroups).  At least four
+  // orbitals a part, as many parts as the tile's accumulators (tc boxes) hold.
+  int occ_parts(int ti, int tj, int tc) const {
+    const int want = (1024 + tj * P.n[0] - 1) / (tj * P.n[0]);
+    return std::max(1, std::min({want, ti / 4, tc / tj}));
   }
 
   // Live plane columns of the pair buffer (FOCK_PRUNE=0: every column).
@@ -776,7 +819,7 @@ struct Engine {
   // target block B.  energy: per-tile FP64 partials into tile_e[tile_base..];
   // apply with acc_full == null: per-target-tile accumulators, each finished
   // into out; apply with acc_full: accumulate into acc_full[nB][N] (zeroed by
-  // the caller, finished by the caller).  sym: A == B at q = 0, tiles I <= J
+  // the caller unless fresh, finished by the caller).  sym: A == B at q = 0, tiles I <= J
   // only, v_ji = conj(v_ij) supplies the mirrored pairs (needs acc_full).
   struct PairJob {
     const void* phiA = nullptr;
@@ -789,6 +832,7 @@ struct Engine {
     double escale = 1.0;
     int tile_base = 0;
     void* acc_full = nullptr;
+    bool fresh = false;  // sym: acc_full is undefined on entry; the first tile of each row overwrites it
     void* out = nullptr;
     int ldo = 0;
     double s0 = 0.0;
@@ -805,7 +849,8 @@ struct Engine {
   };
 
   fock_status pairs(const KernelParams& kp, char* ws, const Layout& L, const PairJob& J, int* ntiles) {
-    const Tiles t = tiles_for(J.nA, J.nB, (int)sizeof(cx<T>));
+    const bool streaming = !J.energy && apply_schedule() == 1;
+    const Tiles t = tiles_for(J.nA, J.nB, (int)sizeof(cx<T>), !J.sym && !J.cross && !streaming);
     void* w = ws + L.w;
     double* epart = reinterpret_cast<double*>(ws + L.epart);
     double* tile_e = reinterpret_cast<double*>(ws + L.tile_e) + J.tile_base;
@@ -872,20 +917,20 @@ struct Engine {
         const int tj = (J.nB - j0) < t.tj ? (J.nB - j0) : t.tj;
         void* acc = J.acc_full ? static_cast<void*>(static_cast<char*>(J.acc_full) + (size_t)j0 * box)
                                : static_cast<void*>(ws + L.acc);
-        if (!J.energy && !J.acc_full) {
-          FX_TRACE(KC_ZERO);
-          FX_HIP(launch_zero<T>(acc, P.N * tj, s));
-        }
+        // the fused pass overwrites the tile's accumulators with its first tile; few
+        // targets: the occupied loop in parts, each with its own accumulators
+        const int split = J.energy || J.acc_full || streaming ? 1 : occ_parts(t.ti, tj, tile_cap(std::max(J.nA, J.nB), (int)sizeof(cx<T>)));
         for (int i0 = 0; i0 < J.nA; i0 += t.ti, ++tile) {
           const int ti = (J.nA - i0) < t.ti ? (J.nA - i0) : t.ti;
           PlaneArgs la = plane_args(J.phiA, J.phiB, w, acc, J.fA, i0, j0, ti, tj);
           la.live = live();
-          if ((st = tile_forward(la, kp, J.energy, epart, PLANE_PAIR_FWD, apply_schedule() == 1)) != FOCK_OK)
-            return st;
+          la.first = !J.acc_full && i0 == 0;
+          la.split = split;
+          if ((st = tile_forward(la, kp, J.energy, epart, PLANE_PAIR_FWD, streaming)) != FOCK_OK) return st;
           if (J.energy) {
             FX_TRACE(KC_REDUCE);
             FX_HIP(launch_energy_tile(epart, ngroups, J.fA, J.gB, i0, j0, ti, tj, 0, 0, J.escale, tile_e + tile, s));
-          } else if (apply_schedule() == 1) {
+          } else if (streaming) {
             {
               FX_TRACE(KC_P3);
               PlaneArgs lv = plane_args(nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0);
@@ -908,15 +953,16 @@ struct Engine {
             ma.ti = ti;
             ma.tj = tj;
             ma.mirror = 0;
+            ma.first = la.first;
             FX_TRACE(KC_P3B);
             FX_HIP(launch_mac_pair<T>(ma, s));
           } else {
             FX_TRACE(KC_P3);
-            FX_HIP(launch_plane<T>(PLANE_INV_MAC, P.n[1], P.n[2], la, tj * P.n[0], s));
+            FX_HIP(launch_plane<T>(PLANE_INV_MAC, P.n[1], P.n[2], la, split * tj * P.n[0], s));
           }
         }
         if (!J.energy && !J.acc_full &&
-            (st = finish(acc, tj, j0, J.out, J.ldo, J.s0, J.wout, J.gscale)) != FOCK_OK)
+            (st = finish(acc, tj, j0, J.out, J.ldo, J.s0, J.wout, J.gscale, split)) != FOCK_OK)
           return st;
       }
       if (ntiles) *ntiles = tile;
@@ -937,6 +983,9 @@ struct Engine {
         // (schedules 1 and 2) the mirror supplies the rest, in an energy the
         // reduction counts the off-diagonal pairs twice
         la.tri = i0 == j0 && ti == tj && (J.energy || sym_schedule() != 0);
+        // the forward half of the tiles i0 = 0 is the first to reach each row J:
+        // mirrors of earlier tiles end at rows below j0
+        la.first = J.fresh && i0 == 0;
         const int tt = la.tri ? tri_slot(0, ti) : ti * tj;
         if ((st = tile_forward(la, kp, J.energy, epart, PLANE_PAIR_FWD, sym_schedule() == 1)) != FOCK_OK) return st;
         if (J.energy) {
@@ -1004,6 +1053,7 @@ struct Engine {
         ma.tj = tj;
         ma.mirror = i0 != j0 || la.tri;
         ma.tri = la.tri;
+        ma.first = la.first;
         FX_TRACE(KC_P3B);
         FX_HIP(launch_mac_pair<T>(ma, s));
       }
@@ -1026,9 +1076,13 @@ fock_status apply_impl(const fock_cell* cell, const Plan& P, const double q[3], 
   void* phiA = ws + L.phiA;
   void* phiB = ws + L.phiB;
   const bool same = occ->c == tgt->c && occ->nb == tgt->nb && occ->ld == tgt->ld;
-  if ((st = E.to_real_space(occ->c, occ->ld, occ->nb, phiA)) != FOCK_OK) return st;
-  if (same) phiB = phiA;
-  else if ((st = E.to_real_space(tgt->c, tgt->ld, tgt->nb, phiB)) != FOCK_OK) return st;
+  if (same) {
+    phiB = phiA;
+    st = E.to_real_space(occ->c, occ->ld, occ->nb, phiA);
+  } else {
+    st = E.to_real_space2(occ, phiA, tgt, phiB);
+  }
+  if (st != FOCK_OK) return st;
   typename Engine<T>::PairJob J;
   J.phiA = phiA;
   J.fA = occ->w;
@@ -1045,7 +1099,8 @@ fock_status apply_impl(const fock_cell* cell, const Plan& P, const double q[3], 
   if (J.sym || occ->nb == 0) {
     // every target accumulates in the (then unused) phiB region; finished once
     J.acc_full = ws + L.phiB;
-    {
+    J.fresh = true;
+    if (occ->nb == 0) {
       FX_TRACE_S(KC_ZERO);
       FX_HIP(launch_zero<T>(J.acc_full, P.N * tgt->nb, s));
     }
@@ -1084,10 +1139,6 @@ fock_status apply_gamma_impl(const fock_cell* cell, const Plan& P, const fock_or
     FX_HIP(launch_sphere<T>(SPHERE_INV_PACK, P.n[0], sa, g, s));
   }
   if ((st = E.plane_sphere(PLANE_INV, pk, m)) != FOCK_OK) return st;
-  {
-    FX_TRACE_S(KC_ZERO);
-    FX_HIP(launch_zero<T>(acc, P.N * m, s));
-  }
   const KernelParams kp = E.kparams(q0, true, cell, d_k0);
   for (int j0 = 0; j0 < m; j0 += kGammaTj) {
     const int tj = std::min(kGammaTj, m - j0);
@@ -1096,6 +1147,7 @@ fock_status apply_gamma_impl(const fock_cell* cell, const Plan& P, const fock_or
       PlaneArgs la = E.plane_args(pk, pk, ws + L.w, nullptr, o->w, i0, j0, ti, tj);
       la.live = E.live();
       la.nreal = n;
+      la.first = i0 == 0;  // the first tile to reach the packed targets j0 ..
       // diagonal tile (the occupied reals of the packed targets): only the
       // pairs with a non-zero weight, i <= 2q + 1, are transformed
       la.tri = i0 == 2 * j0;
@@ -1122,6 +1174,7 @@ fock_status apply_gamma_impl(const fock_cell* cell, const Plan& P, const fock_or
         ma.ti = ti;
         ma.tj = tj;
         ma.tri = la.tri;
+        ma.first = la.first;
         FX_TRACE(KC_P3B);
         FX_HIP(launch_mac_gamma<T>(ma, n, s));
         continue;
@@ -1166,9 +1219,13 @@ fock_status energy_impl(const fock_cell* cell, const Plan& P, const double q[3],
   void* phiA = ws + L.phiA;
   void* phiB = ws + L.phiB;
   const bool same = occ->c == tgt->c && occ->nb == tgt->nb && occ->ld == tgt->ld;
-  if ((st = E.to_real_space(occ->c, occ->ld, occ->nb, phiA)) != FOCK_OK) return st;
-  if (same) phiB = phiA;
-  else if ((st = E.to_real_space(tgt->c, tgt->ld, tgt->nb, phiB)) != FOCK_OK) return st;
+  if (same) {
+    phiB = phiA;
+    st = E.to_real_space(occ->c, occ->ld, occ->nb, phiA);
+  } else {
+    st = E.to_real_space2(occ, phiA, tgt, phiB);
+  }
+  if (st != FOCK_OK) return st;
   typename Engine<T>::PairJob J;
   J.phiA = phiA;
   J.fA = occ->w;
@@ -2151,7 +2208,7 @@ fock_status batch_create(BatchPlanImpl& B, const std::string& cache) {
     std::memcpy(S.kp.b, P.b, sizeof(S.kp.b));
     S.kp.q[0] = S.kp.q[1] = S.kp.q[2] = 0.0;
     S.kp.ecut = B.cells[k].ecut_fock;
-    S.kp.k0 = B.d_k0 + k;
+    S.kp.k0 = B.cells[k].g0 == FOCK_G0_ZERO ? nullptr : B.d_k0 + k;
     S.kp.q_zero = 1;
     S.N = P.N;
     S.n = P.n[0];

@@ -48,7 +48,7 @@ struct KernelParams {
   double b[3][3];      // reciprocal lattice vectors (rows), bohr^-1
   double q[3];         // bohr^-1
   double ecut;         // cutoff on |q+G|^2; <= 0: none
-  const double* k0;    // device scalar: K at q+G = 0 (only used when q_zero)
+  const double* k0;    // device scalar: K at q+G = 0 (only used when q_zero; null: 0)
   int q_zero;
 };
 
@@ -66,6 +66,12 @@ struct PlaneArgs {
   int n1, nb;
   double fscale;       // constant factor on f in P3
   int store_v;         // P3: also write the real-space v back into the pair buffer
+  int first;           // P3, forward half: overwrite acc (its first tile), else add
+  int split;           // P3 (PLANE_INV_MAC): the occupied loop in `split` parts, part s into the
+                       // accumulator rows s tj .. of acc; PLANE_FWD: sum `split` boxes, sstride apart,
+                       // while reading (0: 1)
+  long long sstride;   // PLANE_FWD: elements between the boxes summed
+  void* x2;            // PLANE_INV: boxes nb .. of the launch (a second block), or null
   int nreal;           // Gamma modes: number of real orbitals (packed arrays hold ceil(nreal / 2))
   int tri;             // diagonal tile of a self-application (i0 == j0, ti == tj): only the
                        // pairs ii <= jj, pair buffer slot tri_slot(ii, jj)
@@ -315,10 +321,16 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     // ii < jj, so each unordered pair reaches each accumulator once.
     constexpr bool mir = MODE == PLANE_INV_MAC_MIR;
     const int nblk = mir ? A.ti : A.tj, nloop = mir ? A.tj : A.ti;
-    const int i1 = lid / nblk, bi = lid - (lid / nblk) * nblk;
+    const int nsp = !mir && A.split > 1 ? A.split : 1;
+    const int i1 = lid / (nblk * nsp), row = lid - i1 * (nblk * nsp);  // accumulator row
+    const int sp = row / nblk, bi = row - sp * nblk;
     const int o0 = mir ? A.j0 : A.i0;
     const cx<T>* src = reinterpret_cast<const cx<T>*>(mir ? A.bsrc : A.a);
-    const int k0 = A.tri && mir ? bi + 1 : 0, k1 = A.tri && !mir ? bi + 1 : nloop;
+    int k0 = A.tri && mir ? bi + 1 : 0, k1 = A.tri && !mir ? bi + 1 : nloop;
+    if (nsp > 1) {  // never on a diagonal tile
+      k0 = nloop * sp / nsp;
+      k1 = nloop * (sp + 1) / nsp;
+    }
     stage();
     // every entry is read here: skipping the dead columns (zeros) measured
     // slower in these register-heavy passes than reading them
@@ -354,11 +366,15 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
         });
       }
     }
-    cx<T>* pc = reinterpret_cast<cx<T>*>(A.acc) + (long long)bi * N + (long long)i1 * PLANE;
-    for_outputs<R1>(t, [&](int e, int row, int col) {
-      const int p = row * N3 + col;
-      pc[p] = cadd<T>(pc[p], s[e]);
-    });
+    cx<T>* pc = reinterpret_cast<cx<T>*>(A.acc) + (long long)row * N + (long long)i1 * PLANE;
+    if (!mir && A.first) {
+      for_outputs<R1>(t, [&](int e, int row, int col) { pc[row * N3 + col] = s[e]; });
+    } else {
+      for_outputs<R1>(t, [&](int e, int row, int col) {
+        const int p = row * N3 + col;
+        pc[p] = cadd<T>(pc[p], s[e]);
+      });
+    }
   } else if constexpr (MODE == PLANE_INV_MAC_G || MODE == PLANE_INV_MAC_MIR_G) {
     // Gamma tiles: real occupied i = i0 + ii, packed targets q = j0 + jj with
     // v = v_{i,2q} + i v_{i,2q+1}.  Each unordered pair counts once per
@@ -427,16 +443,24 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       });
     } else {
       cx<T>* pc = reinterpret_cast<cx<T>*>(A.acc) + (long long)bi * N + (long long)i1 * PLANE;
-      for_outputs<R1>(t, [&](int e, int row, int col) {
-        const int p = row * N3 + col;
-        pc[p] = cadd<T>(pc[p], s[e]);
-      });
+      if (A.first) {
+        for_outputs<R1>(t, [&](int e, int row, int col) { pc[row * N3 + col] = s[e]; });
+      } else {
+        for_outputs<R1>(t, [&](int e, int row, int col) {
+          const int p = row * N3 + col;
+          pc[p] = cadd<T>(pc[p], s[e]);
+        });
+      }
     }
   } else if constexpr (MODE == PLANE_FWD) {
     const int ob = lid / A.n1, i1 = lid - (lid / A.n1) * A.n1;
     cx<T>* px = reinterpret_cast<cx<T>*>(A.x) + (long long)ob * N + (long long)i1 * PLANE;
     for_inputs<R0>(t, [&](int e, int row, int col) { v[e] = px[row * N3 + col]; });
     stage();
+    for (int q = 1; q < A.split; ++q) {
+      const cx<T>* pq = px + q * A.sstride;
+      for_inputs<R0>(t, [&](int e, int row, int col) { v[e] = cadd<T>(v[e], pq[row * N3 + col]); });
+    }
     pass_compute<R0, -1, T>(v, tw3, t);
     exchange<R0, R1, N3, SPLIT, T, PAD>(v, smem, t);
     pass_compute<R1, -1, T>(v, tw3, t);
@@ -451,7 +475,9 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     });
   } else {  // PLANE_INV
     const int ob = lid / A.n1, i1 = lid - (lid / A.n1) * A.n1;
-    cx<T>* px = reinterpret_cast<cx<T>*>(A.x) + (long long)ob * N + (long long)i1 * PLANE;
+    const bool second = A.x2 && ob >= A.nb;
+    cx<T>* px = reinterpret_cast<cx<T>*>(second ? A.x2 : A.x) + (long long)(second ? ob - A.nb : ob) * N +
+                (long long)i1 * PLANE;
     const int hc = A.live ? A.live[t % N3] : N2;  // pair buffers: entries outside are zero
     for_inputs<C0>(t, [&](int e, int row, int col) {
       v[e] = live_row<N2>(row, hc) ? px[row * N3 + col] : mk<T>(T(0), T(0));
@@ -630,7 +656,7 @@ __device__ __forceinline__ void pencil_body(const PencilArgs& A, int lid, unsign
     constexpr bool energy = MODE == PENCIL_FE;
     const KernelParams& kp = A.kp;
     double esum = 0.0;
-    const double k0 = kp.q_zero ? *kp.k0 : 0.0;
+    const double k0 = kp.q_zero && kp.k0 ? *kp.k0 : 0.0;
     const typename P1::Lane l = P1::lane(t);
 #pragma unroll
     for (int s = 0; s < P1::NS; ++s) {
@@ -748,6 +774,7 @@ struct MacArgs {
   long long N;
   int i0, j0, ti, tj, mirror;
   int tri;             // diagonal tile: pairs ii <= jj at tri_slot(ii, jj); forward ii <= jj, mirror ii < jj
+  int first;           // the forward half overwrites acc_b (its first tile), else adds
 };
 
 constexpr int kMacTile = 16;  // the persistent batch schedule's and the Gamma path's tile edge
@@ -782,7 +809,7 @@ __global__ __launch_bounds__(256) void mac_pair_kernel(MacArgs A) {
   }
   for (int jj = 0; jj < tj; ++jj) {
     const long long oj = (long long)(A.j0 + jj) * N;
-    const cx<T> aj0 = acc_b[oj];
+    const cx<T> aj0 = A.first ? mk<T>(T(0), T(0)) : acc_b[oj];
     // the forward half alone (mirror == 0) reads neither phi_b nor f_b
     const cx<T> fphi_j = mirror ? cscale<T>(phi_b[oj], T(f_b[A.j0 + jj])) : mk<T>(T(0), T(0));
     const int iend = tri ? jj + 1 : ti;  // forward: ii < iend; mirror: ii < jj on a diagonal tile
@@ -849,7 +876,7 @@ __global__ __launch_bounds__(256) void mac_gamma_kernel(MacArgs A, int nreal) {
     const bool two = j1r < nreal;
     const long long oq = (long long)q * N;
     const cx<T> P = pk[oq];
-    const cx<T> a0 = acc[oq];
+    const cx<T> a0 = A.first ? mk<T>(T(0), T(0)) : acc[oq];
     const T fj0 = T(f[j0r]), fj1 = two ? T(f[j1r]) : T(0);
     // diagonal tile: only ii < gtri_count(ti, jj) is stored, from gtri_prefix(ti, jj)
     const int iend = A.tri ? gtri_count(ti, jj) : ti;

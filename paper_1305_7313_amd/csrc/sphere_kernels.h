@@ -54,6 +54,9 @@ struct SphereArgs {
   int n2, n3, ngrp;     // ngrp: workgroups per box
   const void* c;        // coefficients in (SPHERE_INV*; SPHERE_FORCE: rows j0 ..)
   int ldc;
+  void* box2;           // SPHERE_INV: boxes nb1 .. of the launch, a second block (nb1 = 0: none)
+  const void* c2;
+  int ldc2, nb1;
   int nreal;            // SPHERE_INV_PACK: number of real orbitals
   void* out;            // coefficients out
   int ldo;
@@ -90,12 +93,14 @@ __global__ __launch_bounds__(W) void sphere_kernel(SphereArgs A) {
   const bool act = li < A.tab.nl;
   const int cc = li * LINE + t % LINE;
   const int p = act ? A.tab.lines[li] * LINE + t % LINE : 0;
-  cx<T>* box = reinterpret_cast<cx<T>*>(A.box) + (long long)pr * A.N + p;
+  const bool second = MODE == SPHERE_INV && A.nb1 > 0 && pr >= A.nb1;
+  cx<T>* box = reinterpret_cast<cx<T>*>(second ? A.box2 : A.box) + (long long)(second ? pr - A.nb1 : pr) * A.N + p;
   cx<T> v[G::NV];
   if constexpr (inv) {
     int idx[P0::NV];
     for_inputs<P0>(t, [&](int e, int row, int) { idx[e] = act ? A.tab.coef[row * ncol + cc] : -1; });
-    const cx<T>* c = reinterpret_cast<const cx<T>*>(A.c) + (long long)(MODE == SPHERE_INV ? pr : 2 * pr) * A.ldc;
+    const cx<T>* c = second ? reinterpret_cast<const cx<T>*>(A.c2) + (long long)(pr - A.nb1) * A.ldc2
+                            : reinterpret_cast<const cx<T>*>(A.c) + (long long)(MODE == SPHERE_INV ? pr : 2 * pr) * A.ldc;
     const bool two = MODE == SPHERE_INV_PACK && 2 * pr + 1 < A.nreal;
     for_inputs<P0>(t, [&](int e, int, int) {
       cx<T> z = mk<T>(T(0), T(0));

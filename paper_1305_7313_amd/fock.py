@@ -229,6 +229,20 @@ def orbs(c, w, npw=None) -> fock_orbs:
     return o
 
 
+def _targets(c, npw) -> fock_orbs:
+    """fock_orbs of an apply's targets, whose weights are not read (the field
+    must not be null)."""
+    if c.dim() != 2 or c.stride(1) != 1:
+        raise ValueError("coefficients must be [nb, ld] with unit stride along G")
+    if c.shape[0] > 0 and c.shape[1] < npw:
+        raise ValueError(f"coefficients hold {c.shape[1]} plane waves per row, fewer than the sphere's {npw}")
+    o = fock_orbs()
+    o.c = o.w = c.data_ptr() if c.numel() else None
+    o.nb = int(c.shape[0])
+    o.ld = int(c.stride(0)) if c.shape[0] > 1 else int(c.shape[1])
+    return o
+
+
 def _stream(device=None):
     import torch
     return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
@@ -334,8 +348,7 @@ def fock_apply(cell: Cell, q, c_occ, f_occ, c_tgt, out=None, ws=None):
     _like(c_tgt, c_occ, "c_tgt")
     if out is not None:
         _like(out, c_occ, "out")
-    ones = torch.ones(c_tgt.shape[0], dtype=torch.float64, device=c_tgt.device)
-    o, t = orbs(c_occ, f_occ, cell.npw), orbs(c_tgt, ones, cell.npw)
+    o, t = orbs(c_occ, f_occ, cell.npw), _targets(c_tgt, cell.npw)
     if out is None:
         out = torch.empty((c_tgt.shape[0], cell.npw), dtype=c_tgt.dtype, device=c_tgt.device)
     _rows(out, c_occ, "out", t.nb, cell.npw, t.ld)
@@ -356,8 +369,7 @@ def fock_apply_noalloc(cell: Cell, q, c_occ, f_occ, c_tgt, out):
     the caller's [n_tgt, npw] result tensor."""
     import torch
     _like(c_tgt, c_occ, "c_tgt")
-    ones = torch.ones(c_tgt.shape[0], dtype=torch.float64, device=c_tgt.device)
-    o, t = orbs(c_occ, f_occ, cell.npw), orbs(c_tgt, ones, cell.npw)
+    o, t = orbs(c_occ, f_occ, cell.npw), _targets(c_tgt, cell.npw)
     _rows(out, c_occ, "out", t.nb, cell.npw, t.ld)
     _check(lib().fock_apply_noalloc(ctypes.byref(cell.c), _qarr(q), dtype_code(c_occ), ctypes.byref(o),
                                     ctypes.byref(t), out.data_ptr() if out.numel() else None,

@@ -104,3 +104,34 @@ def test_band_chunks(prec, nb):
     e2 = rel_fro(host(F.fock_band_force(cell, k, cd, wd, vd)), bands.band_force(s.a, s.n, s.miller, k, c, w, v))
     report(f"band chunks {prec} {nb}", density=e1, force=e2)
     assert max(e1, e2) < TOL[prec]
+
+
+# few targets: the occupied loop of the fused pass in parts, and tiles wider
+# than the square edge (one target; parts with a remainder; several tiles; the
+# part count at its limit; the streaming schedule of the 96 x 128 FP64 plane)
+@pytest.mark.parametrize("n,prec,nocc,ntgt", [
+    ((24, 24, 24), "c64", 35, 1), ((24, 24, 24), "c128", 70, 3), ((24, 24, 24), "c128", 4, 17),
+    ((48, 48, 48), "c128", 40, 5), ((48, 48, 64), "c64", 70, 17), ((48, 48, 48), "c128", 290, 1),
+    ((96, 96, 128), "c128", 9, 2),
+])
+def test_few_targets(n, prec, nocc, ntgt):
+    from paper_1305_7313_amd import fock as F
+    s = synth.make_system(synth.ortho_cell(*(x / 2.5 for x in n)), n)
+    rng = np.random.default_rng(8)
+    occ = rng.standard_normal((nocc, s.npw)) + 1j * rng.standard_normal((nocc, s.npw))
+    tgt = rng.standard_normal((ntgt, s.npw)) + 1j * rng.standard_normal((ntgt, s.npw))
+    f, g = np.linspace(0.2, 1.0, nocc), np.linspace(1.0, 0.5, ntgt)
+    q = np.array([0.04, -0.01, 0.02])
+    cell = F.Cell(s.a, s.n, s.miller)
+    od, td, fd, gd = dev(occ, _dtype(prec)), dev(tgt, _dtype(prec)), dev(f), dev(g)
+    print(f"[case] few targets {n} {prec} {nocc} x {ntgt}", flush=True)
+    v = host(F.fock_apply(cell, q, od, fd, td))
+    # the oracle on a sample of the targets
+    js = sorted({0, ntgt // 2, ntgt - 1})
+    ref = exx.fock_apply(s.a, s.n, s.miller, q, occ, f, tgt[js])
+    e, er = rel_fro(v[js], ref), max_row_rel(v[js], ref)
+    # E = 1/2 sum_j g_j Re <psi_j | V_x psi_j>, all targets, from a second path
+    ex = float(host(F.fock_energy(cell, q, od, fd, td, gd)))
+    e_v = 0.5 * float(np.sum(g * np.sum(np.conj(tgt) * v.astype(np.complex128), axis=1).real))
+    report(f"few targets {n} {prec} {nocc}x{ntgt}", rel=e, maxband=er, energy=abs(ex - e_v) / abs(ex))
+    assert e < TOL[prec] and er < TOL[prec] and abs(ex - e_v) < TOL[prec] * abs(ex)
