@@ -347,21 +347,26 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       exchange<C1, R0, N3, SPLIT, T, PAD>(v, smem, t);
       pass_compute<R0, +1, T>(v, tw3, t);
       exchange<R0, R1, N3, SPLIT, T, PAD>(v, smem, t);
+      const cx<T>* pa = src + (long long)(o0 + k) * N + (long long)i1 * PLANE;
+      // 24 values per thread: issued together here, since left to itself the
+      // compiler waited for each (9072 against 4640 us on 48 x 32 orbitals)
+      constexpr bool batch = sizeof(T) == 4 && N2 == 96 && N3 == 96;
+      cx<T> ph[R1::NV];
+      if constexpr (batch) for_outputs<R1>(t, [&](int e, int row, int col) { ph[e] = pa[row * N3 + col]; });
       pass_compute<R1, +1, T>(v, tw3, t);
       const T fk = T(A.f[o0 + k] * A.fscale);
-      const cx<T>* pa = src + (long long)(o0 + k) * N + (long long)i1 * PLANE;
       if (!mir && A.store_v) {
         cx<T>* pv = const_cast<cx<T>*>(pw);
         for_outputs<R1>(t, [&](int e, int row, int col) { pv[row * N3 + col] = v[e]; });
       }
       if constexpr (mir) {
         for_outputs<R1>(t, [&](int e, int row, int col) {
-          const cx<T> pr = cmulc<T>(v[e], pa[row * N3 + col]);  // conj(v) phi
+          const cx<T> pr = cmulc<T>(v[e], batch ? ph[e] : pa[row * N3 + col]);  // conj(v) phi
           s[e] = mk<T>(s[e].x + fk * pr.x, s[e].y + fk * pr.y);
         });
       } else {
         for_outputs<R1>(t, [&](int e, int row, int col) {
-          const cx<T> pr = cmul<T>(pa[row * N3 + col], v[e]);
+          const cx<T> pr = cmul<T>(batch ? ph[e] : pa[row * N3 + col], v[e]);
           s[e] = mk<T>(s[e].x + fk * pr.x, s[e].y + fk * pr.y);
         });
       }
@@ -591,12 +596,15 @@ struct PencilTune {
 constexpr PencilTune pencil_tune(int tbytes, int n1, int mode = -1) {
   if (n1 == 24) return PencilTune{64, 128, -1, 1};
   // FP32 P2 on 48- and 64-point pencils: 512 threads (re-timed on a full
-  // 16 x 16 tile: 48: 88 -> 81 us, 64: 191 -> 180 us)
-  if (n1 == 48) return tbytes == 4 && mode == PENCIL_FKI ? PencilTune{64, 512, -1, 1} : PencilTune{64, 128, -1, 1};
+  // 16 x 16 tile: 48: 88 -> 81 us, 64: 191 -> 180 us) within 64 and 80
+  // registers, which is one more workgroup per CU than the 66 and 82 they take
+  // unbounded (64 x 32 orbitals: 670 -> 612 and 1567 -> 1398 us; the 72- and
+  // 96-point pencils spill under the next bound and lose 2% and 35%)
+  if (n1 == 48) return tbytes == 4 && mode == PENCIL_FKI ? PencilTune{64, 512, -1, 8} : PencilTune{64, 128, -1, 1};
   if (n1 == 64) {
     // FP64 P2: 512 threads on an unsplit 66.5 KB tile, two per CU (-3.5%)
     if (tbytes == 8 && mode == PENCIL_FKI) return PencilTune{64, 512, 0, 2};
-    if (mode == PENCIL_FKI) return PencilTune{64, 512, -1, 1};
+    if (mode == PENCIL_FKI) return PencilTune{64, 512, -1, 6};
     return PencilTune{64, 256, -1, 1};
   }
   if (n1 == 72) return tbytes == 4 ? PencilTune{32, 128, -1, 1} : PencilTune{32, 256, -1, 1};
