@@ -415,6 +415,8 @@ fock_status get_plan(const fock_cell* cell, int dtype, std::shared_ptr<Plan>* ou
 // ---------------------------------------------------------------------------
 constexpr int kGbParts = 512;
 
+constexpr int kDotParts = 16;  // parts of a band's dot product
+
 struct Tiles {
   int ti, tj;
 };
@@ -1457,13 +1459,22 @@ fock_status kmesh_impl(const fock_cell* cell, const Plan& P, int nk, const doubl
     }
   }
   if (ex && ex_from_grad) {
-    double* part = reinterpret_cast<double*>(ws + L.tile_e);
+    // the pair energies' region is free here: parts of every band's dot product
+    double* part = reinterpret_cast<double*>(ws + L.epart);
+    const int tc = tile_cap(nbmax, (int)sizeof(cx<T>));
+    long long bands = 0;
+    for (int k = 0; k < nk; ++k) bands += sets[k].nb;
+    const long long room = (long long)tc * tc * E.ngroups;
+    int parts = kDotParts;
+    if (bands * parts > room) parts = (int)std::max<long long>(1, room / std::max<long long>(1, bands));
+    if (bands > room) part = reinterpret_cast<double*>(ws + L.tile_e);  // holds one value per band
     int off = 0;
     for (int k = 0; k < nk; ++k) {
       if (sets[k].nb == 0) continue;
       FX_TRACE(KC_REDUCE);
-      FX_HIP(launch_band_dot<T>(sets[k].c, sets[k].ld, grad[k], sets[k].ld, P.npw, nullptr, sets[k].nb, part + off, s));
-      off += sets[k].nb;
+      FX_HIP(launch_band_dot<T>(sets[k].c, sets[k].ld, grad[k], sets[k].ld, P.npw, nullptr, sets[k].nb, parts,
+                                part + off, s));
+      off += sets[k].nb * parts;
     }
     if (off == 0) {
       FX_HIP(launch_set_scalar(ex, 0.0, s));
@@ -1671,7 +1682,7 @@ struct BatchPlanImpl {
   bool persistent_ok = true;    // every system one block applied to itself at q = 0 on a cubic grid
   std::vector<void*> outs;      // plan-owned [tgt.nb][tgt.ld] results
   double* d_ex = nullptr;       // [nsys] energies
-  double* d_bandE = nullptr;    // per-band energy terms, systems one after another
+  double* d_bandE = nullptr;    // [bands][kDotParts] energy terms, systems one after another
   std::vector<int> band_off;
   std::vector<void*> phi, acc;
   std::vector<void*> allocs;
@@ -1826,9 +1837,9 @@ fock_status batch_energies(BatchPlanImpl& B, hipStream_t s) {
       FX_HIP(launch_set_scalar(B.d_ex + k, 0.0, s));
       continue;
     }
-    double* part = B.d_bandE + B.band_off[k];
-    FX_HIP(launch_band_dot<T>(t.c, t.ld, B.outs[k], t.ld, B.plans[k]->npw, t.w, t.nb, part, s));
-    FX_HIP(launch_energy_final(part, t.nb, 0.5, B.d_ex + k, s));
+    double* part = B.d_bandE + (size_t)B.band_off[k] * kDotParts;
+    FX_HIP(launch_band_dot<T>(t.c, t.ld, B.outs[k], t.ld, B.plans[k]->npw, t.w, t.nb, kDotParts, part, s));
+    FX_HIP(launch_energy_final(part, t.nb * kDotParts, 0.5, B.d_ex + k, s));
   }
   return FOCK_OK;
 }
@@ -2168,7 +2179,7 @@ fock_status batch_create(BatchPlanImpl& B, const std::string& cache) {
   }
   if ((st = B.alloc(&p, sizeof(double) * B.nsys)) != FOCK_OK) return st;
   B.d_ex = static_cast<double*>(p);
-  if ((st = B.alloc(&p, sizeof(double) * (size_t)std::max(nbands, 1))) != FOCK_OK) return st;
+  if ((st = B.alloc(&p, sizeof(double) * kDotParts * (size_t)std::max(nbands, 1))) != FOCK_OK) return st;
   B.d_bandE = static_cast<double*>(p);
   if ((st = B.alloc(&p, sizeof(int))) != FOCK_OK) return st;
   B.d_abort = static_cast<int*>(p);

@@ -29,7 +29,7 @@ hipError_t launch_gather_unpack(const void* box, long long N, const int* slot, i
                                 void* out, int ldo, double s0, hipStream_t s);
 template <typename T> hipError_t launch_mac_gamma(const MacArgs& a, int nreal, hipStream_t s);
 template <typename T>
-hipError_t launch_band_dot(const void* c, int ldc, const void* v, int ldv, int npw, const double* g, int nb,
+hipError_t launch_band_dot(const void* c, int ldc, const void* v, int ldv, int npw, const double* g, int nb, int parts,
                            double* part, hipStream_t s);
 template <typename T> hipError_t launch_sphere(int mode, int n1, const SphereArgs& a, int nblocks, hipStream_t s);
 template <typename T> hipError_t launch_axis2(int dir, int n2, int n3, const Axis2Args& a, int nblocks, hipStream_t s);

@@ -152,10 +152,10 @@ hipError_t launch_mac_gamma<FX_T>(const MacArgs& a, int nreal, hipStream_t s) {
 
 template <>
 hipError_t launch_band_dot<FX_T>(const void* c, int ldc, const void* v, int ldv, int npw, const double* g, int nb,
-                                 double* part, hipStream_t s) {
+                                 int parts, double* part, hipStream_t s) {
   if (nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(band_dot_kernel<FX_T>, dim3(nb), dim3(256), 0, s, reinterpret_cast<const cx<FX_T>*>(c), ldc,
-                     reinterpret_cast<const cx<FX_T>*>(v), ldv, npw, g, part);
+  hipLaunchKernelGGL(band_dot_kernel<FX_T>, dim3(nb, parts), dim3(256), 0, s, reinterpret_cast<const cx<FX_T>*>(c),
+                     ldc, reinterpret_cast<const cx<FX_T>*>(v), ldv, npw, g, part);
   return hipGetLastError();
 }
 
