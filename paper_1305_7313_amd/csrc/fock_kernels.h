@@ -629,7 +629,18 @@ __device__ __forceinline__ void pencil_body(const PencilArgs& A, int lid, unsign
   const int ngroups = plane / CB;
   const int pr = lid / ngroups, g = lid - (lid / ngroups) * ngroups;
   const int c0 = g * CB;
-  cx<T>* base = reinterpret_cast<cx<T>*>(A.x) + (long long)pr * A.N + c0;
+  // Element (row, col) of this thread is at its first row i0 plus a row known at
+  // compile time: a uniform base per row and one 32-bit offset per thread, 61 of
+  // the 96-point pass's 1112 vector instructions and 8 of its 114 registers less
+  // (64 FP32 orbitals on 96^3: 4918 -> 4827 us, 96 x 96 x 128: 6305 -> 6217).
+  char* const base = reinterpret_cast<char*>(reinterpret_cast<cx<T>*>(A.x) + (long long)pr * A.N + c0);
+  const unsigned off0 = unsigned((P0::lane(t).i0 * plane + t % CB) * (int)sizeof(cx<T>));
+  const unsigned off1 = unsigned((P1::lane(t).i0 * plane + t % CB) * (int)sizeof(cx<T>));
+  const auto at = [&](int row, int i0, unsigned off) {
+    return reinterpret_cast<cx<T>*>(base + (size_t)((row - i0) * plane) * sizeof(cx<T>) + off);
+  };
+  const auto in0 = [&](int row) { return at(row, P0::lane(t).i0, off0); };
+  const auto out1 = [&](int row) { return at(row, P1::lane(t).i0, off1); };
   cx<T> v[Cfg::NV];
 
   // (row, col) of the tile = (i1, column c0 + col).  A column pass: every
@@ -646,17 +657,17 @@ __device__ __forceinline__ void pencil_body(const PencilArgs& A, int lid, unsign
   }
   if constexpr (MODE == PENCIL_FKI || MODE == PENCIL_FE)
     for_inputs<P0>(t, [&](int e, int row, int col) {
-      v[e] = live ? load_stream<T>(&base[(long long)row * plane + col]) : mk<T>(T(0), T(0));
+      v[e] = live ? load_stream<T>(in0(row)) : mk<T>(T(0), T(0));
     });
   else
-    for_inputs<P0>(t, [&](int e, int row, int col) { v[e] = base[(long long)row * plane + col]; });
+    for_inputs<P0>(t, [&](int e, int row, int col) { v[e] = *in0(row); });
   stage();
   pass_compute<P0, DIR0, T>(v, tw1, t);
   exchange<P0, P1, CB, SPLIT, T>(v, smem, t);
   pass_compute<P1, DIR0, T>(v, tw1, t);
 
   if constexpr (MODE == PENCIL_FWD || MODE == PENCIL_INV) {
-    for_outputs<P1>(t, [&](int e, int row, int col) { base[(long long)row * plane + col] = v[e]; });
+    for_outputs<P1>(t, [&](int e, int row, int col) { *out1(row) = v[e]; });
     return;
   } else {
     // Coulomb kernel on the natural-order outputs (column c0 + b, k1 = row).
@@ -731,7 +742,7 @@ __device__ __forceinline__ void pencil_body(const PencilArgs& A, int lid, unsign
         st = ((m >> ((threadIdx.x & 63) & ~(LINE - 1))) & ((1ull << LINE) - 1)) != 0;
       }
       if (st)
-        for_outputs<P1>(t, [&](int e, int row, int col) { store_stream<T>(&base[(long long)row * plane + col], v[e]); });
+        for_outputs<P1>(t, [&](int e, int row, int col) { store_stream<T>(out1(row), v[e]); });
     }
   }
 }
