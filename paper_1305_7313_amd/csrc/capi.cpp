@@ -927,7 +927,7 @@ struct Engine {
             lv.x = w;
             lv.live = live();
             lv.nb = ti * tj;
-            FX_HIP(launch_plane<T>(PLANE_INV, P.n[1], P.n[2], lv, ti * tj * P.n[0], s));
+            FX_HIP(launch_plane<T>(PLANE_INV_PAIR, P.n[1], P.n[2], lv, ti * tj * P.n[0], s));
           }
           MacArgs ma{};
           ma.w = w;
@@ -974,7 +974,7 @@ struct Engine {
               lv.x = w;
               lv.live = live();
               lv.nb = ti * tj;
-              FX_HIP(launch_plane<T>(PLANE_INV, P.n[1], P.n[2], lv, ti * tj * P.n[0], s));
+              FX_HIP(launch_plane<T>(PLANE_INV_PAIR, P.n[1], P.n[2], lv, ti * tj * P.n[0], s));
             }
             // acc holds the tile's targets from row 0: target jj at row jj
             MacArgs ma{};
@@ -1073,7 +1073,7 @@ struct Engine {
           lv.x = w;
           lv.live = live();
           lv.nb = tt;
-          FX_HIP(launch_plane<T>(PLANE_INV, P.n[1], P.n[2], lv, tt * P.n[0], s));
+          FX_HIP(launch_plane<T>(PLANE_INV_PAIR, P.n[1], P.n[2], lv, tt * P.n[0], s));
         }
         MacArgs ma{};
         ma.w = w;
@@ -1198,7 +1198,7 @@ fock_status apply_gamma_impl(const fock_cell* cell, const Plan& P, const fock_or
           lv.x = ws + L.w;
           lv.live = E.live();
           lv.nb = tt;
-          FX_HIP(launch_plane<T>(PLANE_INV, P.n[1], P.n[2], lv, tt * P.n[0], s));
+          FX_HIP(launch_plane<T>(PLANE_INV_PAIR, P.n[1], P.n[2], lv, tt * P.n[0], s));
         }
         MacArgs ma{};
         ma.w = ws + L.w;

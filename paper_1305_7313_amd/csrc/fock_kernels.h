@@ -31,6 +31,7 @@ enum PlaneMode : int {
   PLANE_FWD = 2,       // in place, forward (a7)
   PLANE_INV = 3,       // in place, backward (a1)
   PLANE_INV_MAC_MIR = 4,  // P3, mirrored half of the pair-symmetric schedule
+  PLANE_INV_PAIR = 5,  // P3 of the streaming schedule: PLANE_INV of a tile's pairs
   // Gamma point, real orbitals packed two per complex array (P_q = psi_2q + i psi_2q+1)
   PLANE_PAIR_FWD_G = 7,    // P1: phi_i(r) P_q(r), forward plane FFT
   PLANE_INV_MAC_G = 8,     // P3 into the packed targets' accumulators
@@ -478,14 +479,23 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     for_outputs<C1>(t, [&](int e, int row, int col) {
       if (live_line<T, N2>(row, hc, t)) px[row * N3 + col] = v[e];
     });
-  } else {  // PLANE_INV
+  } else {  // PLANE_INV, PLANE_INV_PAIR
     const int ob = lid / A.n1, i1 = lid - (lid / A.n1) * A.n1;
     const bool second = A.x2 && ob >= A.nb;
     cx<T>* px = reinterpret_cast<cx<T>*>(second ? A.x2 : A.x) + (long long)(second ? ob - A.nb : ob) * N +
                 (long long)i1 * PLANE;
     const int hc = A.live ? A.live[t % N3] : N2;  // pair buffers: entries outside are zero
+    // Pairs are read once: their loads carry the hint, which leaves the caches to
+    // the stores (64 orbitals FP32 96 x 96 x 128 6662 -> 6326 us, 72^3 FP64 4041 ->
+    // 3723).  Not with one FP64 96-row plane per CU (96^3 3964 -> 4417, 96 x 128
+    // 3518 -> 3984), nor for orbitals, which the next pass reads again (hinted,
+    // they cost the pair pass 5-10%).
+    constexpr bool hint = MODE == PLANE_INV_PAIR && !(sizeof(T) == 8 && N2 == 96);
     for_inputs<C0>(t, [&](int e, int row, int col) {
-      v[e] = live_row<N2>(row, hc) ? px[row * N3 + col] : mk<T>(T(0), T(0));
+      if constexpr (hint)
+        v[e] = live_row<N2>(row, hc) ? load_stream<T>(&px[row * N3 + col]) : mk<T>(T(0), T(0));
+      else
+        v[e] = live_row<N2>(row, hc) ? px[row * N3 + col] : mk<T>(T(0), T(0));
     });
     stage();
     pass_compute<C0, +1, T>(v, tw2, t);
@@ -508,7 +518,7 @@ struct PlaneTune {
   int minb;  // the launch bound's minimum waves per SIMD
 };
 constexpr PlaneTune plane_tune(int tbytes, int n2, int n3, int mode) {
-  const bool p1 = mode == PLANE_PAIR_FWD || mode == PLANE_PAIR_FWD_G, inv = mode == PLANE_INV,
+  const bool p1 = mode == PLANE_PAIR_FWD || mode == PLANE_PAIR_FWD_G, inv = mode == PLANE_INV || mode == PLANE_INV_PAIR,
              pair = p1 || inv,
              fwdmac = mode == PLANE_INV_MAC || mode == PLANE_INV_MAC_G,
              mirror = mode == PLANE_INV_MAC_MIR || mode == PLANE_INV_MAC_MIR_G,

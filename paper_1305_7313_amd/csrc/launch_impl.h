@@ -18,6 +18,7 @@ hipError_t plane_mode(int mode, const PlaneArgs& a, int nblocks, hipStream_t s) 
     case PLANE_INV_MAC: return plane_go<PLANE_INV_MAC, N2, N3>(a, nblocks, s);
     case PLANE_FWD: return plane_go<PLANE_FWD, N2, N3>(a, nblocks, s);
     case PLANE_INV: return plane_go<PLANE_INV, N2, N3>(a, nblocks, s);
+    case PLANE_INV_PAIR: return plane_go<PLANE_INV_PAIR, N2, N3>(a, nblocks, s);
     case PLANE_INV_MAC_MIR: return plane_go<PLANE_INV_MAC_MIR, N2, N3>(a, nblocks, s);
     case PLANE_PAIR_FWD_G: return plane_go<PLANE_PAIR_FWD_G, N2, N3>(a, nblocks, s);
     case PLANE_INV_MAC_G: return plane_go<PLANE_INV_MAC_G, N2, N3>(a, nblocks, s);

@@ -29,7 +29,7 @@ def kernel_class(name: str):
     m = re.search(r"plane_kernel<\w+, \d+, \d+, \d+, \w+, (\d), \d>", name)
     if m:
         return {"0": "p1_pair_plane_fwd", "1": "p3_plane_inv_mac", "2": "a7_plane_fwd", "3": "plane_inv",
-                "4": "p3_second", "7": "p1_pair_plane_fwd",
+                "4": "p3_second", "5": "p3_plane_inv_mac", "7": "p1_pair_plane_fwd",
                 "8": "p3_plane_inv_mac", "9": "p3_second"}.get(m.group(1))
     m = re.search(r"pencil_kernel<\w+, \d+, \d+, \d+, \w+, (\d), \d>", name)
     if m:
