@@ -274,6 +274,24 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     }
     const cx<T>* pb = reinterpret_cast<const cx<T>*>(A.bsrc) + (long long)(A.j0 + jj) * N + (long long)i1 * PLANE;
     const int hc = A.live ? A.live[t % N3] : N2;  // a column pass: column t % N3 for every stored value
+    // The tile's operand planes of i1 + 1 are brought into L2 by this plane's
+    // workgroups, a word of some lines each: the first users of a plane would all
+    // wait for HBM (16 x 16 FP64 pairs use 2-2.6 MB of planes; P1 of 64 x 32
+    // orbitals on 72^3 3792 -> 3239 us, 128 on 64^3 8465 -> 8252; FP32 and larger
+    // planes lose 0-5%).
+    unsigned ahead = 0;
+    constexpr bool warm = MODE == PLANE_PAIR_FWD && sizeof(T) == 8 && N3 >= 64 && N3 <= 72;
+    if constexpr (warm) {
+      constexpr int LPP = PLANE * (int)sizeof(cx<T>) / 128;  // lines of a plane
+      const int norb = A.tri ? A.tj : A.ti + A.tj;
+      const int per = (norb * LPP + tt - 1) / tt;
+      const int ln = rem * per + t, o = ln / LPP;
+      if (i1 + 1 < A.n1 && t < per && o < norb) {
+        const cx<T>* src = reinterpret_cast<const cx<T>*>(o < A.tj ? A.bsrc : A.a) +
+                           (long long)(o < A.tj ? A.j0 + o : A.i0 + o - A.tj) * N + (long long)(i1 + 1) * PLANE;
+        ahead = *reinterpret_cast<const unsigned*>(reinterpret_cast<const char*>(src) + (size_t)(ln - o * LPP) * 128);
+      }
+    }
     cx<T> b[Cfg::NV];
     if constexpr (MODE == PLANE_PAIR_FWD) {
       const cx<T>* pa = reinterpret_cast<const cx<T>*>(A.a) + (long long)(A.i0 + ii) * N + (long long)i1 * PLANE;
@@ -314,6 +332,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       else st = live_row<N2>(row, hc);
       if (st) store_stream<T>(&pw[row * N3 + col], v[e]);
     });
+    if constexpr (warm) asm volatile("" ::"v"(ahead));  // kept; waited for at the end
   } else if constexpr (MODE == PLANE_INV_MAC || MODE == PLANE_INV_MAC_MIR) {
     // PLANE_INV_MAC: block (jj, i1), loop over ii, acc_j += f_i phi_i v_ij.
     // PLANE_INV_MAC_MIR (one orbital block at q = 0): block (ii, i1), loop over
