@@ -894,6 +894,20 @@ struct Engine {
     const size_t box = (size_t)P.N * sizeof(cx<T>);
     fock_status st;
     int tile = 0;
+    // Jobs whose fused passes read every pair-buffer line: over several tiles the
+    // dead lines are cleared once instead of written by every pencil pass.
+    // Schedule 0 leaves real-space values there.  Self calls, cleared against
+    // written: FP64 64^3 34.39 against 34.86 ms; 48^3 4.48 against 4.49, where the
+    // lines still lie in cache; FP32 24^3 582 against 566 us.
+    const int schedule = J.sym || J.cross ? sym_schedule() : streaming ? 1 : 2;
+    const auto parts = [](int n, int e) { return (n + e - 1) / e; };
+    const int tiles = J.sym ? parts(J.nB, t.tj) * (parts(J.nB, t.tj) + 1) / 2 : parts(J.nA, t.ti) * parts(J.nB, t.tj);
+    bool masked = schedule == 1;
+    if (!J.energy && schedule == 2 && tiles > 2 && P.n[2] >= 64 && live()) {
+      FX_TRACE(KC_ZERO);
+      FX_HIP(launch_clear_dead<T>(w, live(), P.n[1], P.n[2], t.ti * t.tj * P.n[0], s));
+      masked = true;
+    }
     if (J.cross) {
       if (J.energy || J.sym || !J.acc_full || !J.acc_mirror || !J.fB || sym_schedule() == 0)
         return fail(FOCK_E_ARG, "internal: bad cross-block job");
@@ -904,9 +918,7 @@ struct Engine {
           const int ti = (J.nA - i0) < T0 ? (J.nA - i0) : T0;
           PlaneArgs la = plane_args(J.phiA, J.phiB, w, nullptr, J.fA, i0, j0, ti, tj);
           la.live = live();
-          // schedule 2 reads the pairs in the fused passes (every column), else
-          // the in-place inverse reads them (live columns only)
-          if ((st = tile_forward(la, kp, false, nullptr, PLANE_PAIR_FWD, sym_schedule() != 2)) != FOCK_OK) return st;
+          if ((st = tile_forward(la, kp, false, nullptr, PLANE_PAIR_FWD, masked)) != FOCK_OK) return st;
           if (sym_schedule() == 2) {
             PlaneArgs lp = la;
             lp.acc = static_cast<char*>(J.acc_full) + (size_t)j0 * box;
@@ -963,7 +975,7 @@ struct Engine {
           la.live = live();
           la.first = !J.acc_full && i0 == 0;
           la.split = split;
-          if ((st = tile_forward(la, kp, J.energy, epart, PLANE_PAIR_FWD, streaming)) != FOCK_OK) return st;
+          if ((st = tile_forward(la, kp, J.energy, epart, PLANE_PAIR_FWD, masked)) != FOCK_OK) return st;
           if (J.energy) {
             FX_TRACE(KC_REDUCE);
             FX_HIP(launch_energy_tile(epart, ngroups, J.fA, J.gB, i0, j0, ti, tj, 0, 0, J.escale, tile_e + tile, s));
@@ -1024,7 +1036,7 @@ struct Engine {
         // mirrors of earlier tiles end at rows below j0
         la.first = J.fresh && i0 == 0;
         const int tt = la.tri ? tri_slot(0, ti) : ti * tj;
-        if ((st = tile_forward(la, kp, J.energy, epart, PLANE_PAIR_FWD, sym_schedule() == 1)) != FOCK_OK) return st;
+        if ((st = tile_forward(la, kp, J.energy, epart, PLANE_PAIR_FWD, masked)) != FOCK_OK) return st;
         if (J.energy) {
           FX_TRACE(KC_REDUCE);
           FX_HIP(launch_energy_tile(epart, ngroups, J.fA, J.gB, i0, j0, ti, tj, 1, la.tri, J.escale, tile_e + tile, s));

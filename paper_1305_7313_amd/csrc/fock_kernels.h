@@ -983,6 +983,29 @@ __global__ __launch_bounds__(256) void mac_conj_kernel(PlaneArgs A, int plane) {
 // ---------------------------------------------------------------------------
 // Small kernels
 // ---------------------------------------------------------------------------
+// Zeros in the 128-byte lines of dead columns of every plane of a pair buffer
+// (one workgroup per plane).  The fused P3 passes read every line, but P1 stores
+// none of these and P2 need not: cleared once per call they stay zero for all
+// its tiles.  128 orbitals FP64 64^3, P2 of 36 tiles: 10387 -> 9651 us, for a
+// clear of 0.18 GB.
+template <typename T>
+__global__ __launch_bounds__(256) void clear_dead_kernel(cx<T>* w, const signed char* __restrict__ live, int n2, int n3) {
+  constexpr int LINE = 128 / (int)sizeof(cx<T>);
+  const int plane = n2 * n3;
+  cx<T>* x = w + (long long)blockIdx.x * plane;
+  for (int p0 = 0; p0 < plane; p0 += 256) {
+    const int p = p0 + threadIdx.x;
+    bool lv = true;
+    if (p < plane) {
+      const int i2 = p / n3, h = live[p - i2 * n3];
+      lv = i2 <= h || i2 >= n2 - h;
+    }
+    const unsigned long long m = __ballot(lv);
+    const bool any = ((m >> ((threadIdx.x & 63) & ~(LINE - 1))) & ((1ull << LINE) - 1)) != 0;
+    if (!any) x[p] = mk<T>(T(0), T(0));
+  }
+}
+
 template <typename T>
 __global__ void zero_kernel(cx<T>* p, long long n) {
   const long long stride = (long long)gridDim.x * blockDim.x;

@@ -114,6 +114,14 @@ hipError_t launch_zero<FX_T>(void* p, long long n, hipStream_t s) {
 }
 
 template <>
+hipError_t launch_clear_dead<FX_T>(void* w, const signed char* live, int n2, int n3, int nplanes, hipStream_t s) {
+  if (nplanes <= 0) return hipSuccess;
+  hipLaunchKernelGGL(clear_dead_kernel<FX_T>, dim3(nplanes), dim3(256), 0, s, reinterpret_cast<cx<FX_T>*>(w), live, n2,
+                     n3);
+  return hipGetLastError();
+}
+
+template <>
 hipError_t launch_scatter<FX_T>(const void* c, int ldc, const int* slot, int npw, int nb, void* box, long long N,
                                 hipStream_t s) {
   if (nb <= 0 || npw <= 0) return hipSuccess;

@@ -135,3 +135,47 @@ def test_few_targets(n, prec, nocc, ntgt):
     e_v = 0.5 * float(np.sum(g * np.sum(np.conj(tgt) * v.astype(np.complex128), axis=1).real))
     report(f"few targets {n} {prec} {nocc}x{ntgt}", rel=e, maxband=er, energy=abs(ex - e_v) / abs(ex))
     assert e < TOL[prec] and er < TOL[prec] and abs(ex - e_v) < TOL[prec] * abs(ex)
+
+
+# a workspace full of NaN: no pass reads a line that this call has not written
+# (dead columns cleared once for several tiles; sphere lines; first tiles that
+# overwrite their accumulators)
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("n,nb", [((24, 24, 24), 70), ((48, 48, 48), 35), ((64, 64, 64), 34), ((72, 72, 72), 18)])
+def test_stale_workspace(n, nb, prec):
+    import torch
+    from paper_1305_7313_amd import fock as F
+    s = synth.make_system(synth.ortho_cell(*(x / 3.0 for x in n)), n)
+    c = synth.random_orbitals(s.a, s.miller, nb, 9)
+    f = np.linspace(0.3, 1.0, nb)
+    cell = F.Cell(s.a, s.n, s.miller)
+    cd, fd = dev(c, _dtype(prec)), dev(f)
+    q0, q1 = np.zeros(3), np.array([0.03, -0.02, 0.05])
+    code = F.dtype_code(cd)
+
+    def nan(nbytes):
+        return torch.full((nbytes // 8,), float("nan"), dtype=torch.float64, device="cuda").view(torch.uint8)
+
+    print(f"[case] stale workspace {n} {prec} {nb}", flush=True)
+    js = [0, nb // 2, nb - 1]
+    size = F.fock_workspace_size(cell, code, nb, nb)
+    own = host(F.fock_apply(cell, q0, cd, fd, cd, ws=nan(size)))[js]
+    e1 = rel_fro(own, exx.fock_apply(s.a, s.n, s.miller, q0, c, f, c[js]))
+    k = nb // 2
+    other = host(F.fock_apply(cell, q1, cd, fd, cd[:k].clone(), ws=nan(size)))[[0, k - 1]]
+    e2 = rel_fro(other, exx.fock_apply(s.a, s.n, s.miller, q1, c, f, c[[0, k - 1]]))
+    ex = float(host(F.fock_energy(cell, q0, cd, fd, cd, fd, ws=nan(size))))
+    vx = host(F.fock_apply(cell, q0, cd, fd, cd, ws=nan(size)))
+    e3 = abs(ex - 0.5 * float(np.sum(f * np.sum(np.conj(c) * vx, axis=1).real))) / abs(ex)
+    g = synth.gamma_orbitals(s.a, s.miller, 19, 4)
+    gd, hd = dev(g, _dtype(prec)), dev(f[:19] if nb >= 19 else np.ones(19))
+    lib = F.lib()
+    import ctypes
+    gsize = int(lib.fock_workspace_size_gamma(ctypes.byref(cell.c), code, 19))
+    gv = host(F.fock_apply_gamma(cell, gd, hd, ws=nan(gsize)))[[0, 18]]
+    e4 = rel_fro(gv, exx.fock_apply(s.a, s.n, s.miller, q0, g, host(hd), g[[0, 18]]))
+    bsize = int(lib.fock_band_workspace_size(ctypes.byref(cell.c), code, nb))
+    rho = host(F.fock_band_density(cell, cd, fd, ws=nan(bsize)))
+    e5 = abs(rho.sum() * s.volume / np.prod(n) - f.sum()) / f.sum()
+    report(f"stale {n} {prec} {nb}", self=e1, other=e2, energy=e3, gamma=e4, charge=e5)
+    assert max(e1, e2, e3, e4, e5) < TOL[prec]
