@@ -894,16 +894,15 @@ struct Engine {
     const size_t box = (size_t)P.N * sizeof(cx<T>);
     fock_status st;
     int tile = 0;
-    // Jobs whose fused passes read every pair-buffer line: over several tiles the
-    // dead lines are cleared once instead of written by every pencil pass.
-    // Schedule 0 leaves real-space values there.  Self calls, cleared against
-    // written: FP64 64^3 34.39 against 34.86 ms; 48^3 4.48 against 4.49, where the
-    // lines still lie in cache; FP32 24^3 582 against 566 us.
+    // P2 leaves the dead lines unwritten where every reader masks them.  For the
+    // fused passes that read every line they are cleared once over several tiles
+    // (FP64 96^3, 48 x 32 orbitals: 26.82 -> 26.26 ms; 72^3, 64 x 32: 13.40 -> 13.10).
+    // Schedule 0 leaves real-space values there.
     const int schedule = J.sym || J.cross ? sym_schedule() : streaming ? 1 : 2;
     const auto parts = [](int n, int e) { return (n + e - 1) / e; };
     const int tiles = J.sym ? parts(J.nB, t.tj) * (parts(J.nB, t.tj) + 1) / 2 : parts(J.nA, t.ti) * parts(J.nB, t.tj);
-    bool masked = schedule == 1;
-    if (!J.energy && schedule == 2 && tiles > 2 && P.n[2] >= 64 && live()) {
+    bool masked = schedule == 1 || (schedule == 2 && fused_masks(sizeof(T), P.n[2]));
+    if (!J.energy && schedule == 2 && !masked && tiles > 2 && live()) {
       FX_TRACE(KC_ZERO);
       FX_HIP(launch_clear_dead<T>(w, live(), P.n[1], P.n[2], t.ti * t.tj * P.n[0], s));
       masked = true;

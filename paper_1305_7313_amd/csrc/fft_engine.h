@@ -48,6 +48,25 @@ template <typename T> __device__ __forceinline__ cx<T> load_stream(const cx<T>* 
   r.y = x.y;
   return r;
 }
+// A range of memory read through a buffer descriptor: a read past its end gives
+// zero and no traffic.  `base` is the same in every lane of a wave.
+struct Window {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Window(const void* base, int bytes)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000)) {}
+};
+// Entry p of the window if `on`, else zero without a read or a branch.
+template <typename T> __device__ __forceinline__ cx<T> load_window(const Window& w, int p, bool on) {
+  constexpr int NT = 2;  // the non-temporal hint
+  const int off = on ? p * (int)sizeof(cx<T>) : -1;
+  if constexpr (sizeof(T) == 8) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b128(w.r, off, 0, NT);
+    return __builtin_bit_cast(cx<T>, x);
+  } else {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b64(w.r, off, 0, NT);
+    return __builtin_bit_cast(cx<T>, x);
+  }
+}
 template <typename T> __device__ __forceinline__ void store_stream(cx<T>* p, cx<T> v) {
   using V = T __attribute__((ext_vector_type(2)));
   V x = {v.x, v.y};

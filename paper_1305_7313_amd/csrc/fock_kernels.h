@@ -95,6 +95,15 @@ template <typename T, int N2> __device__ __forceinline__ bool live_line(int i2, 
   return ((m >> ((t & 63) & ~(LINE - 1))) & ((1ull << LINE) - 1)) != 0;
 }
 
+// Do the fused P3 passes read only the live entries of a pair?  A load that is
+// skipped by a branch or moved to a line of zeros costs these register-heavy
+// passes more than the dead bytes (FP64 64^3 8328 -> 11206 us), one that the
+// buffer's bounds check answers costs nothing: FP64 64 8162 -> 7640, 48 1188 ->
+// 1140, FP32 96 4557 -> 4200; FP32 48 to 72 0-3% more, which P2 gives back where
+// it need not write the dead lines.  The FP64 passes on 72 and 96 points spill
+// registers and lose 9% and 28%: they read every line.
+constexpr bool fused_masks(int tbytes, int n3) { return tbytes == 4 || n3 <= 64; }
+
 // How P1 walks a tile and stores its partly live lines.
 // strip: the workgroups of one plane take `strip` occupied orbitals at a time
 //   against every target.  The operand planes in flight on one XCD are then
@@ -351,16 +360,21 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       k0 = nloop * sp / nsp;
       k1 = nloop * (sp + 1) / nsp;
     }
+    constexpr bool masks = fused_masks(sizeof(T), N3);
+    const int hc = masks && A.live ? A.live[t % N3] : N2;  // entries outside are zero: not read
     stage();
-    // every entry is read here: skipping the dead columns (zeros) measured
-    // slower in these register-heavy passes than reading them
     cx<T> s[R1::NV];
 #pragma unroll
     for (int e = 0; e < R1::NV; ++e) s[e] = mk<T>(T(0), T(0));
     for (int k = k0; k < k1; ++k) {
       const int slot = A.tri ? (mir ? tri_slot(bi, k) : tri_slot(k, bi)) : (mir ? bi * A.tj + k : k * A.tj + bi);
       const cx<T>* pw = reinterpret_cast<const cx<T>*>(A.w) + (long long)slot * N + (long long)i1 * PLANE;
-      for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = load_stream<T>(&pw[row * N3 + col]); });
+      if constexpr (masks) {
+        const Window win(pw, PLANE * (int)sizeof(cx<T>));
+        for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = load_window<T>(win, row * N3 + col, live_row<N2>(row, hc)); });
+      } else {
+        for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = load_stream<T>(&pw[row * N3 + col]); });
+      }
       pass_compute<C0, +1, T>(v, tw2, t);
       exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
       pass_compute<C1, +1, T>(v, tw2, t);
@@ -429,9 +443,8 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       const int j0r = 2 * q, j1r = 2 * q + 1;
       const int slot = A.tri ? gtri_prefix(A.ti, jj) + ii : ii * A.tj + jj;
       const cx<T>* pw = reinterpret_cast<const cx<T>*>(A.w) + (long long)slot * N + (long long)i1 * PLANE;
-      for_inputs<C0>(t, [&](int e, int row, int col) {
-        v[e] = live_row<N2>(row, hc) ? load_stream<T>(&pw[row * N3 + col]) : mk<T>(T(0), T(0));
-      });
+      const Window win(pw, PLANE * (int)sizeof(cx<T>));
+      for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = load_window<T>(win, row * N3 + col, live_row<N2>(row, hc)); });
       pass_compute<C0, +1, T>(v, tw2, t);
       exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
       pass_compute<C1, +1, T>(v, tw2, t);
@@ -984,10 +997,10 @@ __global__ __launch_bounds__(256) void mac_conj_kernel(PlaneArgs A, int plane) {
 // Small kernels
 // ---------------------------------------------------------------------------
 // Zeros in the 128-byte lines of dead columns of every plane of a pair buffer
-// (one workgroup per plane).  The fused P3 passes read every line, but P1 stores
-// none of these and P2 need not: cleared once per call they stay zero for all
-// its tiles.  128 orbitals FP64 64^3, P2 of 36 tiles: 10387 -> 9651 us, for a
-// clear of 0.18 GB.
+// (one workgroup per plane).  Fused P3 passes without masks (fused_masks) read
+// every line, but P1 stores none of these and P2 need not: cleared once per call
+// they stay zero for all its tiles.  P2 writing them in each of 36 tiles of FP64
+// 64^3 took 10387 us, without 9651, for a clear of 0.18 GB.
 template <typename T>
 __global__ __launch_bounds__(256) void clear_dead_kernel(cx<T>* w, const signed char* __restrict__ live, int n2, int n3) {
   constexpr int LINE = 128 / (int)sizeof(cx<T>);
