@@ -48,14 +48,21 @@ template <typename T> __device__ __forceinline__ cx<T> load_stream(const cx<T>* 
   r.y = x.y;
   return r;
 }
-// A range of memory read through a buffer descriptor: a read past its end gives
-// zero and no traffic.  `base` is the same in every lane of a wave.
+// A range of memory behind a buffer descriptor: a read past its end gives zero, a
+// write there nothing, neither any traffic.  `base` is the same in every lane of a
+// wave; the first lane's is taken, so that the compiler need not loop over lanes
+// where it cannot tell.
 struct Window {
   __amdgpu_buffer_rsrc_t r;
-  __device__ __forceinline__ Window(const void* base, int bytes)
-      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000)) {}
+  __device__ __forceinline__ Window(const void* base, int bytes) {
+    const unsigned long long a = reinterpret_cast<unsigned long long>(base);
+    const unsigned long long lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+    const unsigned long long hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+    r = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(hi << 32 | lo), 0, bytes, 0x00020000);
+  }
 };
-// Entry p of the window if `on`, else zero without a read or a branch.
+// Entry p of the window if `on`, else zero without a read or a branch; a store
+// of it if `on`.
 template <typename T> __device__ __forceinline__ cx<T> load_window(const Window& w, int p, bool on) {
   constexpr int NT = 2;  // the non-temporal hint
   const int off = on ? p * (int)sizeof(cx<T>) : -1;
@@ -65,6 +72,17 @@ template <typename T> __device__ __forceinline__ cx<T> load_window(const Window&
   } else {
     const auto x = __builtin_amdgcn_raw_buffer_load_b64(w.r, off, 0, NT);
     return __builtin_bit_cast(cx<T>, x);
+  }
+}
+template <typename T> __device__ __forceinline__ void store_window(const Window& w, int p, bool on, cx<T> v) {
+  constexpr int NT = 2;
+  const int off = on ? p * (int)sizeof(cx<T>) : -1;
+  if constexpr (sizeof(T) == 8) {
+    using V = unsigned __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(V, v), w.r, off, 0, NT);
+  } else {
+    using V = unsigned __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), w.r, off, 0, NT);
   }
 }
 template <typename T> __device__ __forceinline__ void store_stream(cx<T>* p, cx<T> v) {

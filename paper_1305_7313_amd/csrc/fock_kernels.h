@@ -118,15 +118,19 @@ constexpr bool fused_masks(int tbytes, int n3) { return tbytes == 4 || n3 <= 64;
 // 96 4552 / 4884 (strip 8: 4458), 96 x 128 13723 / 14864 (strip 8: 13330);
 // FP64 48 931 / 793, 64 8538 / 8913, 72 3688 / 4070, 96 4429 / 4236 (strip 4:
 // 4165), 96 x 128 9036 / 8723 (strip 4: 8618).
+// window: the stores' masks as offsets past the end of a buffer descriptor instead
+//   of branches (P1 us, branches against offsets): FP64 64 8045 / 7741, FP32 24
+//   93 / 91, 48 1119 / 1099, 64 2439 / 2381, 72 4648 / 4570; FP64 72 and FP32 96
+//   lose 0-1%, FP64 48 and 96 1-2%, FP32 96 x 128 2.5%.
 struct P1Tune {
   int strip;
-  bool lines;
+  bool lines, window;
 };
 constexpr P1Tune p1_tune(int tbytes, int n2, int n3, bool gamma) {
   // Gamma tiles (128 pairs, half the orbitals) have the bandwidth for the extra
   // bytes also at FP64 64: 1038 / 861
-  if (tbytes == 8) return P1Tune{n3 >= 96 ? 4 : 1, n2 <= 48 || n3 >= 96 || (gamma && n3 == 64)};
-  return P1Tune{n3 >= 96 ? 8 : n3 <= 48 ? 4 : 1, n3 <= 64};
+  if (tbytes == 8) return P1Tune{n3 >= 96 ? 4 : 1, n2 <= 48 || n3 >= 96 || (gamma && n3 == 64), n3 == 64};
+  return P1Tune{n3 >= 96 ? 8 : n3 <= 48 ? 4 : 1, n3 <= 64, n3 <= 72};
 }
 
 // Slot of pair (ii, jj), ii <= jj, in the pair buffer of a diagonal tile.
@@ -261,6 +265,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     // workgroup (i1, slot): slot = ii * tj + jj, or on a diagonal tile
     // tri_slot(ii, jj) (gtri_prefix(ti, jj) + ii in the Gamma modes)
     constexpr bool gam = MODE == PLANE_PAIR_FWD_G;
+    constexpr P1Tune tn = p1_tune(sizeof(T), N2, N3, gam);
     const int tt = A.tri ? (gam ? gtri_prefix(A.ti, A.tj) : A.ti * (A.ti + 1) / 2) : A.ti * A.tj;
     const int i1 = lid / tt, rem = lid - i1 * tt;
     int ii, jj;
@@ -275,7 +280,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
       ii = rem - tri_slot(0, jj);
     } else {
       // strips of occupied orbitals, the targets walked inside a strip (P1Tune)
-      constexpr int S = p1_tune(sizeof(T), N2, N3, gam).strip;
+      constexpr int S = tn.strip;
       const int strip = rem / (S * A.tj), r = rem - strip * (S * A.tj);
       const int h = A.ti - strip * S < S ? A.ti - strip * S : S;
       jj = r / h;
@@ -333,13 +338,15 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     pass_compute<C1, -1, T>(v, tw2, t);
     const int slot = A.tri ? rem : ii * A.tj + jj;
     cx<T>* pw = reinterpret_cast<cx<T>*>(A.w) + (long long)slot * N + (long long)i1 * PLANE;
+    const Window win(pw, PLANE * (int)sizeof(cx<T>));
     // Dead entries are not stored, or (P1Tune::lines) a 128-byte line with a
     // live entry is written whole: the dead entries' values are never read.
     for_outputs<C1>(t, [&](int e, int row, int col) {
       bool st;
-      if constexpr (p1_tune(sizeof(T), N2, N3, gam).lines) st = live_line<T, N2>(row, hc, t);
+      if constexpr (tn.lines) st = live_line<T, N2>(row, hc, t);
       else st = live_row<N2>(row, hc);
-      if (st) store_stream<T>(&pw[row * N3 + col], v[e]);
+      if constexpr (tn.window) store_window<T>(win, row * N3 + col, st, v[e]);
+      else if (st) store_stream<T>(&pw[row * N3 + col], v[e]);
     });
     if constexpr (warm) asm volatile("" ::"v"(ahead));  // kept; waited for at the end
   } else if constexpr (MODE == PLANE_INV_MAC || MODE == PLANE_INV_MAC_MIR) {
