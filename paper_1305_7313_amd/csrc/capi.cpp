@@ -843,13 +843,18 @@ struct Engine {
   // Gamma tiles: 0 = fused inverse plane FFT + MAC passes (forward, then a
   // recomputing mirror); 1 = in-place inverse plane FFT of the tile, then one
   // streaming pass for both halves.  The fused passes hold a whole plane per
-  // block; from 72-point-wide planes they spill (FP64) or lose occupancy
-  // (FP32), and the streaming schedule is faster in both precisions.
+  // block: from 72-point-wide planes they spill (FP64) or lose occupancy (FP32;
+  // 60 orbitals on 72^3 4994 against 3912 us).  On 48-point planes the tile is
+  // small and one streaming pass for both halves is the less work: FP64 6 / 16 /
+  // 64 orbitals 90 / 258 / 2648 fused against 81 / 215 / 2495 us, FP32 16 / 120
+  // 164 / 5140 against 148 / 5122.  On 64 and 24 points the fused passes stay
+  // ahead (FP64 64 orbitals 4410 against 4936, 723 against 927).
   int gamma_schedule() const {
     const char* e = std::getenv("FOCK_GAMMA_SCHEDULE");
     const int env = e ? std::atoi(e) : -1;
     if (env == 0 || env == 1) return env;
-    return std::max(P.n[1], P.n[2]) >= 72 ? 1 : 0;
+    const int n = std::max(P.n[1], P.n[2]);
+    return n >= 72 || n == 48 ? 1 : 0;
   }
 
   // One band-pair job: occupied block A (real space, weights fA) against
