@@ -100,8 +100,9 @@ template <typename T, int N2> __device__ __forceinline__ bool live_line(int i2, 
 // passes more than the dead bytes (FP64 64^3 8328 -> 11206 us), one that the
 // buffer's bounds check answers costs nothing: FP64 64 8162 -> 7640, 48 1188 ->
 // 1140, FP32 96 4557 -> 4200; FP32 48 to 72 0-3% more, which P2 gives back where
-// it need not write the dead lines.  The FP64 passes on 72 and 96 points spill
-// registers and lose 9% and 28%: they read every line.
+// it need not write the dead lines.  The FP64 passes on 72 and 96 points have no
+// registers left for the masks and lose 9% and 28%: they read every line (through
+// the descriptor too, whose one base spares 96^3 27 of 48 spills, 1%).
 constexpr bool fused_masks(int tbytes, int n3) { return tbytes == 4 || n3 <= 64; }
 
 // How P1 walks a tile and stores its partly live lines.
@@ -119,9 +120,10 @@ constexpr bool fused_masks(int tbytes, int n3) { return tbytes == 4 || n3 <= 64;
 // FP64 48 931 / 793, 64 8538 / 8913, 72 3688 / 4070, 96 4429 / 4236 (strip 4:
 // 4165), 96 x 128 9036 / 8723 (strip 4: 8618).
 // window: the stores' masks as offsets past the end of a buffer descriptor instead
-//   of branches (P1 us, branches against offsets): FP64 64 8045 / 7741, FP32 24
-//   93 / 91, 48 1119 / 1099, 64 2439 / 2381, 72 4648 / 4570; FP64 72 and FP32 96
-//   lose 0-1%, FP64 48 and 96 1-2%, FP32 96 x 128 2.5%.
+//   of branches (P1 us, branches against offsets): FP64 64 8045 / 7741.  FP64 72
+//   and FP32 96 lose 0-1%, FP64 48 and 96 1-2%, FP32 96 x 128 2.5%.  FP32 up to
+//   72 points gain 1.5-2.5% but keep the branches: without them the last butterfly
+//   is contracted to other fused multiply-adds, which moves energies by up to 1e-9.
 struct P1Tune {
   int strip;
   bool lines, window;
@@ -130,7 +132,7 @@ constexpr P1Tune p1_tune(int tbytes, int n2, int n3, bool gamma) {
   // Gamma tiles (128 pairs, half the orbitals) have the bandwidth for the extra
   // bytes also at FP64 64: 1038 / 861
   if (tbytes == 8) return P1Tune{n3 >= 96 ? 4 : 1, n2 <= 48 || n3 >= 96 || (gamma && n3 == 64), n3 == 64};
-  return P1Tune{n3 >= 96 ? 8 : n3 <= 48 ? 4 : 1, n3 <= 64, n3 <= 72};
+  return P1Tune{n3 >= 96 ? 8 : n3 <= 48 ? 4 : 1, n3 <= 64, false};
 }
 
 // Slot of pair (ii, jj), ii <= jj, in the pair buffer of a diagonal tile.
@@ -376,12 +378,10 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     for (int k = k0; k < k1; ++k) {
       const int slot = A.tri ? (mir ? tri_slot(bi, k) : tri_slot(k, bi)) : (mir ? bi * A.tj + k : k * A.tj + bi);
       const cx<T>* pw = reinterpret_cast<const cx<T>*>(A.w) + (long long)slot * N + (long long)i1 * PLANE;
-      if constexpr (masks) {
-        const Window win(pw, PLANE * (int)sizeof(cx<T>));
-        for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = load_window<T>(win, row * N3 + col, live_row<N2>(row, hc)); });
-      } else {
-        for_inputs<C0>(t, [&](int e, int row, int col) { v[e] = load_stream<T>(&pw[row * N3 + col]); });
-      }
+      const Window win(pw, PLANE * (int)sizeof(cx<T>));
+      for_inputs<C0>(t, [&](int e, int row, int col) {
+        v[e] = load_window<T>(win, row * N3 + col, !masks || live_row<N2>(row, hc));
+      });
       pass_compute<C0, +1, T>(v, tw2, t);
       exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
       pass_compute<C1, +1, T>(v, tw2, t);
@@ -513,6 +513,7 @@ __device__ __forceinline__ void plane_body(const PlaneArgs& A, int lid, unsigned
     pass_compute<C0, -1, T>(v, tw2, t);
     exchange<C0, C1, N3, SPLIT, T, PAD>(v, smem, t);
     pass_compute<C1, -1, T>(v, tw2, t);
+    settle<C1>(v, t);
     // live (sphere columns): only the lines the sphere pencils read are stored
     const int hc = A.live ? A.live[t % N3] : N2;
     for_outputs<C1>(t, [&](int e, int row, int col) {

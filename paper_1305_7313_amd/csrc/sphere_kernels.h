@@ -123,6 +123,7 @@ __global__ __launch_bounds__(W) void sphere_kernel(SphereArgs A) {
   pass_compute<P0, DIR, T>(v, tw1, t);
   exchange<P0, P1, CB, SPLIT, T>(v, smem, t);
   pass_compute<P1, DIR, T>(v, tw1, t);
+  settle<P1>(v, t);
   if (!act) return;
   if constexpr (inv || MODE == SPHERE_FWD_BOX) {
     for_outputs<P1>(t, [&](int e, int row, int) { box[(long long)row * plane] = v[e]; });
