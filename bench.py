@@ -249,23 +249,27 @@ def step_bytes(nb, N, bpc, fp64, sym=True, sched=None, lf=1.0, n=None, flops=Non
             # diagonal tiles of schedules 1 and 2 hold only the pairs ii <= jj
             tri = diag and sched != 0
             npr = ti * (ti + 1) // 2 if tri else ti * tj
-            # P1 stores and P2 reads only the live columns (fraction lf); P2
-            # writes the dead columns' zeros only for the fused P3 passes
-            # (schedules 0 and 2), which read every column
+            # P1 stores and P2 reads only the live columns (fraction lf), and so
+            # do P2's stores and the inverse passes' reads (fraction rd), except
+            # with fused P3 passes on FP64 planes beyond 64 points, which read
+            # every column
             f = pf or {k: 0.0 for k in ("p1_pair_plane_fwd", "p2_pencil_kernel", "p3_inplace", "p3_fused", "mac_half")}
             nmir = (ti * (ti - 1) // 2 if tri else 0) if diag else ti * tj  # pairs of the mirror half
             add("p1_pair_plane_fwd", ti + (0 if diag else tj), npr * lf, fl=npr * f["p1_pair_plane_fwd"])
-            add("p2_pencil_kernel", npr * lf, npr * lf if sym and sched == 1 else npr, fl=npr * f["p2_pencil_kernel"])
+            fused = not sym or sched != 1
+            rd = lf if not fused or (n is not None and (not fp64 or n[2] <= 64)) else 1.0
+            add("p2_pencil_kernel", npr * lf, npr * (1.0 if sym and sched == 0 else rd), fl=npr * f["p2_pencil_kernel"])
             if not sym:
-                add("p3_plane_inv_mac", ti * tj + ti + tj, tj, fl=npr * f["p3_fused"])
+                add("p3_plane_inv_mac", ti * tj * rd + ti + tj, tj, fl=npr * f["p3_fused"])
             elif sched in (0, 2):  # fused P3 into acc_J; mirror: recomputed (2) or from v written back (0)
-                add("p3_plane_inv_mac", npr + ti + tj, tj + (ti * tj if sched == 0 and not diag else 0),
+                add("p3_plane_inv_mac", npr * rd + ti + tj, tj + (ti * tj if sched == 0 and not diag else 0),
                     fl=npr * f["p3_fused"])
                 mfl = nmir * (f["p3_fused"] if sched == 2 else f["mac_half"])
+                md = rd if sched == 2 else 1.0  # schedule 0's second pass reads v in real space
                 if not diag:
-                    add("p3_second", ti * tj + tj + ti, ti, fl=mfl)
+                    add("p3_second", ti * tj * md + tj + ti, ti, fl=mfl)
                 elif tri and ti > 1:
-                    add("p3_second", ti * (ti - 1) // 2 + tj + ti, ti, fl=mfl)
+                    add("p3_second", ti * (ti - 1) // 2 * md + tj + ti, ti, fl=mfl)
             else:  # schedule 1: in-place inverse (reads the live columns), one MAC for both halves
                 add("p3_plane_inv_mac", npr * lf, npr, fl=npr * f["p3_inplace"])
                 add("p3_second", npr + ti + (0 if diag else tj) + tj + ti, tj + (0 if diag and not tri else ti),
